@@ -11,12 +11,13 @@ import shutil
 import subprocess
 import sys
 import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libA2T.so")
-SOURCES = ["kernels.hip", "a2t.cpp", "distill.hip"]
+SOURCES = ["kernels.hip", "attn_block.hip", "a2t.cpp", "distill.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
@@ -44,11 +45,12 @@ def build(verbose: bool = False) -> str:
     """Compile every source and link libA2T.so; returns its path."""
     tmpdir = tempfile.mkdtemp(prefix="a2t_build_")
     try:
-        objs = []
-        for src in SOURCES:
-            obj = os.path.join(tmpdir, src + ".o")
-            _run([HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj], verbose)
-            objs.append(obj)
+        objs = [os.path.join(tmpdir, src + ".o") for src in SOURCES]
+        with ThreadPoolExecutor(len(SOURCES)) as pool:
+            jobs = [pool.submit(_run, [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj], verbose)
+                    for src, obj in zip(SOURCES, objs)]
+            for j in jobs:
+                j.result()
         tmp_lib = os.path.join(tmpdir, "libA2T.so")
         _run([HIPCC, *FLAGS, "-shared", *objs, "-o", tmp_lib], verbose)
         shutil.move(tmp_lib, LIB + ".tmp")

@@ -386,6 +386,52 @@ void plan_splits(a2t_cache* c, int n, const int* tiles, const int64_t* floats_pe
     c->plan_splits.assign(splits, splits + n);
 }
 
+constexpr int kBlockTilesPerCu = 6;
+
+// Whether a launch runs on attn_block instead of attn_tile, which takes kBlockRows
+// query rows per KV head in one pass over its keys and every further kBlockRows in
+// another.  Past two passes attn_block is the faster one, with its separate append
+// (36 layers' shape, 4 layers a step: 70 rows onto 500 keys 94 against 117 us, 1,024
+// onto 4,096 354 against 1,943).  With two passes it is where the launch has several
+// tiles per CU to walk (160 query rows, 8 streams of ~2,400 keys: 185 against 234 us);
+// below that attn_tile's key splits fill the GPU and the append's launch costs more
+// (132 query rows, one stream of 4,096 keys: 88 against 82 us; 4 tiles per CU: 127
+// against 124).
+bool many_rows(const a2t_cache* c, int n, const int32_t* ids, const int32_t* n_q) {
+    if (c->cfg.dtype != A2T_BF16 || c->force_valu) return false;
+    const int G = c->cfg.n_q_heads / c->cfg.n_kv_heads;
+    int rows = 0;
+    int64_t tiles = 0;
+    for (int i = 0; i < n; ++i) {
+        rows = std::max(rows, n_q[i]);
+        tiles += (c->ss[ids[i]].resident() + kTileKeys - 1) / kTileKeys;
+    }
+    return G * rows > 2 * kBlockRows ||
+           (G * rows > kBlockRows && tiles * c->cfg.n_kv_heads >= (int64_t)kBlockTilesPerCu * c->target_wgs);
+}
+
+// Key splits of an attn_block launch: none where its query blocks fill the CUs,
+// else the fewest tiles per split (at least kBlockMinTiles) whose workgroups
+// still fit one round.
+constexpr int kBlockMinTiles = 4;
+void plan_block_splits(const a2t_cache* c, int n, const int* tiles, const int32_t* n_q,
+                       const int64_t* floats_per_split, int* splits, int64_t ws_limit) {
+    const int Hkv = c->cfg.n_kv_heads, G = c->cfg.n_q_heads / Hkv;
+    int max_tiles = 1;
+    for (int i = 0; i < n; ++i) max_tiles = std::max(max_tiles, tiles[i]);
+    for (int budget = std::min(kBlockMinTiles, max_tiles); budget <= max_tiles; ++budget) {
+        int64_t wgs = 0, ws = 0;
+        for (int i = 0; i < n; ++i) {
+            const int want = c->force_splits > 0 ? std::min(c->force_splits, tiles[i]) : (tiles[i] + budget - 1) / budget;
+            splits[i] = std::max(1, std::min(want, kMaxSplits));
+            wgs += (int64_t)splits[i] * Hkv * ((G * n_q[i] + kBlockRows - 1) / kBlockRows);
+            ws += stream_partials(splits[i], floats_per_split[i]);
+        }
+        if ((wgs <= c->target_wgs || c->force_splits > 0) && ws <= ws_limit) return;
+    }
+    std::fill(splits, splits + n, 1);
+}
+
 // Where a launch's split partials go: the cache's workspace (default) or the
 // library's fixed device array (the no-allocation entry point, which plans
 // without the workspace limit and never times its launches).
@@ -441,7 +487,11 @@ int attn_launch(a2t_cache* c, int layer, int n, const int32_t* ids, const int32_
         max_rows = std::max(max_rows, n_q[i]);
         floats[i] = (int64_t)c->cfg.n_kv_heads * G * n_q[i] * rf;
     }
-    plan_splits(c, n, tiles, floats, nsplit, wsc ? INT64_MAX : c->dev.ws_floats);
+    const bool block = !in_row0 && many_rows(c, n, ids, n_q);
+    if (block)
+        plan_block_splits(c, n, tiles, n_q, floats, nsplit, wsc ? wsc->floats : c->dev.ws_floats);
+    else
+        plan_splits(c, n, tiles, floats, nsplit, wsc ? INT64_MAX : c->dev.ws_floats);
     // descriptors in order of falling tiles per split: the dispatcher starts the
     // longest workgroups first
     int ord[kMaxDesc];
@@ -514,6 +564,11 @@ int attn_launch(a2t_cache* c, int layer, int n, const int32_t* ids, const int32_
     b.max_splits = splits;
     b.max_rows = max_rows;
     hipError_t e;
+    auto launch = [&](const DevState& st, const KTimer& kt) {
+        if (valu) return launch_attn_valu(st, b, q, o, c->stream, kt);
+        if (block) return launch_attn_block(st, b, q, o, c->target_wgs, c->stream, kt);
+        return launch_attn_tile(st, b, q, o, k_in, v_in, c->stream, kt);
+    };
     if (wsc) {
         // the caller checked the partials against the fixed array before any state changed
         if (off > wsc->floats) return A2T_ERR_CAPACITY;
@@ -521,15 +576,13 @@ int attn_launch(a2t_cache* c, int layer, int n, const int32_t* ids, const int32_
         st.ws = wsc->ws;
         st.ws_floats = wsc->floats;
         const KTimer none{};
-        e = valu ? launch_attn_valu(st, b, q, o, c->stream, none)
-                 : launch_attn_tile(st, b, q, o, k_in, v_in, c->stream, none);
+        e = launch(st, none);
         if (e == hipSuccess && splits > 1) e = launch_attn_merge(st, b, o, c->stream, none, !valu);
         return e == hipSuccess ? A2T_OK : hip_fail(c);
     }
     {
-        ProfScope ps(c, valu ? "attn_valu" : "attn_tile");
-        e = valu ? launch_attn_valu(c->dev, b, q, o, c->stream, ps.kt())
-                 : launch_attn_tile(c->dev, b, q, o, k_in, v_in, c->stream, ps.kt());
+        ProfScope ps(c, valu ? "attn_valu" : block ? "attn_block" : "attn_tile");
+        e = launch(c->dev, ps.kt());
     }
     if (e != hipSuccess) return hip_fail(c);
     if (splits > 1) {
@@ -963,7 +1016,11 @@ int append_attn_impl(a2t_cache* c, int32_t layer, int32_t n_streams, const int32
                      const int32_t* n_rows, const void* kin, const void* vin, const uint8_t* seg,
                      const int32_t* pos, const int32_t* unit_id, const int32_t* n_q, const void* q,
                      void* o, const WsChoice* wsc) {
-    const bool fused = c->cfg.dtype == A2T_BF16 && !c->force_valu;
+    // steps of many query rows append first and then run attn_block: each of its
+    // query blocks would otherwise rotate the step's keys again
+    bool fused = c->cfg.dtype == A2T_BF16 && !c->force_valu;
+    for (int i0 = 0; i0 < n_streams && fused; i0 += kMaxDesc)
+        fused = !many_rows(c, std::min(kMaxDesc, n_streams - i0), ids + i0, n_q + i0);
     int rc = append_impl(c, layer, n_streams, ids, n_rows, kin, vin, seg, pos, unit_id, !fused);
     if (rc) return rc;
     if (!fused) return attn_common(c, layer, n_streams, ids, n_q, q, o, false, wsc);

@@ -20,6 +20,8 @@ constexpr int kTileKeys = 64;
 constexpr int kMaxSplits = 128;
 // Query rows per workgroup of the split merge.
 constexpr int kMergeRows = 4;
+// Query rows (G * n_q rows of a KV head) per workgroup of attn_block.
+constexpr int kBlockRows = 128;
 
 // State of one stream kept on the device for device-planned steps (the host's
 // per-stream mirror, moved to the device while the caller drives the cache
@@ -211,6 +213,11 @@ hipError_t launch_append(const DevState& st, const AppendBatch& b, int n_layers,
 hipError_t launch_attn_tile(const DevState& st, const AttnBatch& b, const void* q, void* o,
                             const void* k_in, const void* v_in, hipStream_t stream,
                             const KTimer& kt);
+// MFMA chunk attention over blocks of kBlockRows query rows (bf16 cache, D 64 or
+// 128; the step's rows already stored).  cus: workgroups that run at once with
+// one per CU; split partials as launch_attn_tile's.
+hipError_t launch_attn_block(const DevState& st, const AttnBatch& b, const void* q, void* o, int cus,
+                             hipStream_t stream, const KTimer& kt);
 // VALU attention, one (row, kv head) per workgroup column (fp32 caches, decode).
 hipError_t launch_attn_valu(const DevState& st, const AttnBatch& b, const void* q, void* o,
                             hipStream_t stream, const KTimer& kt);

@@ -23,6 +23,7 @@
 //               eviction mask and compaction indices over the whole cache.
 #include "a2t_internal.h"
 #include "a2t.h"
+#include "device_common.h"
 
 #include <hip/hip_ext.h>
 #include <math.h>
@@ -35,11 +36,6 @@ namespace {
 
 constexpr uint8_t kSegAcoustic = 1;
 constexpr uint8_t kSegDelim = 2;
-
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 struct bf16_t {
     uint16_t bits;
@@ -329,18 +325,8 @@ __global__ __launch_bounds__(256) void attn_valu_kernel(DevState st, BT b, const
 // operand reads the same keys of V.  No cross-lane transposes of P.
 constexpr int kMfmaThreads = 512;
 
-__device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
-    typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
-    const bf16x2 v = {(__bf16)a, (__bf16)b};   // v_cvt_pk_bf16_f32, round to nearest even
-    return __builtin_bit_cast(uint32_t, v);
-}
-
 // max / sum over the four lanes l, l^16, l^32, l^48 (the lanes holding one
 // query column of a 16x16 accumulator), with the gfx950 row-swap permutes
-__device__ __forceinline__ uint32_t pack_f16x2(float a, float b) {
-    return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)a) |
-           ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)b) << 16);
-}
 __device__ __forceinline__ float quad_max(float x) {
     const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
@@ -376,34 +362,6 @@ struct TileBuf {
 
 typedef short short4_t __attribute__((ext_vector_type(4)));
 
-// s_waitcnt vmcnt(N) with expcnt and lgkmcnt left alone (gfx9 encoding)
-template <int N>
-__device__ __forceinline__ void wait_vmem() {
-    static_assert(N >= 0 && N < 64, "vmcnt range");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-// workgroup barrier that the compiler may not move memory accesses across; no
-// memory fence (the waits that make DMA'd data visible are explicit)
-__device__ __forceinline__ void barrier_only() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-__device__ __forceinline__ void dma16(const void* src, uint16_t* lds) {
-    __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
-}
-__device__ __forceinline__ uint32_t lds_addr(const void* p) {
-    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)(p);
-}
-// Transposed LDS read issued as inline assembly: the compiler cannot tell which
-// LDS the builtin form reads and would wait for every outstanding DMA before
-// it.  The result is valid only after lds_wait_all() names it.
-template <int OFF>
-__device__ __forceinline__ uint2 lds_tr16_issue(uint32_t addr) {
-    uint2 r;
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "i"(OFF));
-    return r;
-}
 // s_waitcnt lgkmcnt(0) that the listed values depend on
 __device__ __forceinline__ void lds_wait_all(uint2 (&a)[8], uint2 (&b)[8]) {
     asm volatile("s_waitcnt lgkmcnt(0)"
@@ -417,14 +375,6 @@ __device__ __forceinline__ void lds_wait_all(uint2 (&a)[4], uint2 (&b)[4]) {
                    "+v"(b[3]));
 }
 
-// 16-byte LDS read issued as inline assembly (the compiler keeps only a few
-// in flight and waits after each pair); valid only after k_wait() names it
-template <int OFF>
-__device__ __forceinline__ u32x4 lds_b128_issue(uint32_t addr) {
-    u32x4 r;
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "i"(OFF));
-    return r;
-}
 // s_waitcnt lgkmcnt(N) that the listed K operands depend on: LDS reads
 // complete in order, so with N reads issued after them these are complete
 template <int N>

@@ -1,0 +1,106 @@
+"""GPU parity of chunk attention with many query rows per KV head (attn_block), against
+the fp64 oracle at every step: row counts around the 128-row blocks and the 256-row
+threshold of the dispatch, one to eight query heads per KV head, both head dims, key
+counts around the 64-key tiles, a ring that wraps, a kept region, forced and planned
+key splits, fewer queries than rows, and batches whose streams differ.
+
+Bar: 2e-2 for bf16 caches with fp32 accumulation, as everywhere in this suite.
+"""
+import dataclasses
+import os
+
+import pytest
+
+from synth.streams import CONFIGS, SEG_ACOUSTIC, SEG_DELIM, SEG_TEXT, tiny_stream
+from tests.harness import Lockstep, row_bounds
+
+pytestmark = pytest.mark.gpu
+
+BF16_TOL = 2e-2
+
+
+def _long(n):
+    """A unit of n rows: mostly acoustic, some transcript rows among them."""
+    return [SEG_TEXT if r % 9 == 4 else SEG_ACOUSTIC for r in range(n)]
+
+
+SMALL = [SEG_ACOUSTIC] * 7 + [SEG_DELIM, SEG_TEXT, SEG_TEXT, SEG_DELIM]
+
+
+@pytest.mark.parametrize("hq,hkv,d,rows,prefix,splits,fused,query_rows", [
+    (4, 1, 128, 65, 0, None, True, None),      # 260 query rows: just past the threshold
+    (8, 2, 64, 96, 5, None, False, None),      # 384: whole blocks
+    (8, 2, 128, 97, 64, "1", True, None),      # 388, no splits, a tile-aligned prefix
+    (2, 2, 64, 257, 1, "3", False, None),      # one query head per KV head
+    (16, 2, 128, 33, 130, "5", True, None),    # eight query heads: 264
+    (6, 3, 64, 200, 63, None, True, None),     # two query heads, three KV heads
+    (8, 2, 128, 150, 0, None, False, 70),      # the last 70 of 150 rows query
+    (4, 1, 64, 129, 0, "128", False, None),    # more splits asked for than tiles
+])
+def test_long_chunks(gpu, hq, hkv, d, rows, prefix, splits, fused, query_rows):
+    cfg = dataclasses.replace(CONFIGS[0], n_q_heads=hq, n_kv_heads=hkv, head_dim=d)
+    spec = tiny_stream([SMALL, _long(rows), SMALL, _long(rows), _long(rows + 1), SMALL, _long(rows)], prefix=prefix)
+    # the ring holds two long units: it wraps, and each long step evicts an older unit
+    bounds = row_bounds(spec)
+    old = os.environ.get("A2T_SPLITS")
+    if splits:
+        os.environ["A2T_SPLITS"] = splits
+    try:
+        ls = Lockstep(cfg, 5, [spec], layers_checked=[0], n_layers=2, budgets=[rows + 40], window=0,
+                      unit_rows=2 * rows + 40 + prefix, kept_rows=bounds[1] + 1, max_step=bounds[2],
+                      tol=BF16_TOL, dtype="bf16", fused=fused, query_rows=query_rows)
+    finally:
+        if splits:
+            if old is None:
+                del os.environ["A2T_SPLITS"]
+            else:
+                os.environ["A2T_SPLITS"] = old
+    try:
+        ls.run()
+    finally:
+        ls.close()
+    print(f"rows {rows}: max attention error {ls.max_err:.2e}, {ls.evictions} evictions", flush=True)
+    assert ls.evictions >= 3
+
+
+@pytest.mark.parametrize("fused", [False, True])
+def test_long_chunks_varlen(gpu, fused):
+    """A batch whose streams have 1 to 150 rows: every stream of the launch runs on the
+    kernel that the longest one asks for."""
+    cfg = dataclasses.replace(CONFIGS[0], n_q_heads=8, n_kv_heads=2, head_dim=128)
+    specs = []
+    for s, rows in enumerate((1, 17, 64, 150)):
+        spec = tiny_stream([SMALL, _long(rows), SMALL, _long(rows)], prefix=40 * s)
+        specs.append(dataclasses.replace(spec, stream=s))
+    ls = Lockstep(cfg, 9, specs, layers_checked=[0, 1], n_layers=2, budgets=[60, 70, 200, 200], window=1,
+                  unit_rows=max(row_bounds(s)[0] for s in specs),
+                  kept_rows=max(row_bounds(s)[1] for s in specs) + 1, max_step=160, tol=BF16_TOL, dtype="bf16",
+                  fused=fused)
+    try:
+        ls.run()
+    finally:
+        ls.close()
+    print(f"varlen: max attention error {ls.max_err:.2e}", flush=True)
+
+
+def test_long_chunks_without_workspace(gpu):
+    """Caches without a split workspace, and the no-allocation entry point: one split per
+    stream where nothing can be split into, the same results."""
+    import numpy as np
+    import torch
+    import paper_2609_31224_amd as a2t
+    rows, hq, hkv, d = 300, 4, 1, 128
+    g = torch.Generator(device="cuda").manual_seed(3)
+    k, v, q = (torch.randn((rows, h, d), generator=g, device="cuda").bfloat16() for h in (hkv, hkv, hq))
+    seg, pos = np.full(rows, SEG_ACOUSTIC, np.uint8), np.arange(rows)
+    outs = []
+    for flags, call in ((0, a2t.a2t_append_attn), (a2t.A2T_FLAG_NO_WORKSPACE, a2t.a2t_append_attn),
+                        (a2t.A2T_FLAG_NO_WORKSPACE, a2t.a2t_append_attn_noalloc)):
+        c = a2t.a2t_cache_create(1, 1, hq, hkv, d, a2t.A2T_BF16, 2 * rows, 8, rows, flags=flags)
+        o = torch.zeros_like(q)
+        call(c, 0, [0], [rows], k, v, seg, pos, [0], [rows], q, o)
+        a2t.a2t_sync(c)
+        outs.append(o.float().cpu().numpy())
+        a2t.a2t_cache_destroy(c)
+    assert np.abs(outs[0] - outs[1]).max() <= BF16_TOL
+    assert np.abs(outs[0] - outs[2]).max() <= BF16_TOL
