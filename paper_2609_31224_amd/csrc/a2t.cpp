@@ -566,7 +566,7 @@ int attn_launch(a2t_cache* c, int layer, int n, const int32_t* ids, const int32_
     hipError_t e;
     auto launch = [&](const DevState& st, const KTimer& kt) {
         if (valu) return launch_attn_valu(st, b, q, o, c->stream, kt);
-        if (block) return launch_attn_block(st, b, q, o, c->target_wgs, c->stream, kt);
+        if (block) return launch_attn_block(st, b, q, o, c->stream, kt);
         return launch_attn_tile(st, b, q, o, k_in, v_in, c->stream, kt);
     };
     if (wsc) {

@@ -214,9 +214,8 @@ hipError_t launch_attn_tile(const DevState& st, const AttnBatch& b, const void* 
                             const void* k_in, const void* v_in, hipStream_t stream,
                             const KTimer& kt);
 // MFMA chunk attention over blocks of kBlockRows query rows (bf16 cache, D 64 or
-// 128; the step's rows already stored).  cus: workgroups that run at once with
-// one per CU; split partials as launch_attn_tile's.
-hipError_t launch_attn_block(const DevState& st, const AttnBatch& b, const void* q, void* o, int cus,
+// 128; the step's rows already stored); split partials as launch_attn_tile's.
+hipError_t launch_attn_block(const DevState& st, const AttnBatch& b, const void* q, void* o,
                              hipStream_t stream, const KTimer& kt);
 // VALU attention, one (row, kv head) per workgroup column (fp32 caches, decode).
 hipError_t launch_attn_valu(const DevState& st, const AttnBatch& b, const void* q, void* o,

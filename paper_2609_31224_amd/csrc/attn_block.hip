@@ -433,13 +433,12 @@ hipError_t by_size(const BT<kMaxDesc>& b, F&& f) {
 
 }  // namespace
 
-hipError_t launch_attn_block(const DevState& st, const AttnBatch& b, const void* q, void* o, int cus,
-                             hipStream_t stream, const KTimer& kt) {
-    int wgs = 0, total = 0;
+hipError_t launch_attn_block(const DevState& st, const AttnBatch& b, const void* q, void* o, hipStream_t stream,
+                             const KTimer& kt) {
+    int wgs = 0;
     for (int i = 0; i < b.count; ++i) {
         const int n = (st.G * b.d[i].n_q + kBlockRows - 1) / kBlockRows * b.d[i].splits * st.Hkv;
         wgs = n > wgs ? n : wgs;
-        total += n;
     }
     const dim3 grid(wgs, 1, b.count);
     const uint16_t* qq = static_cast<const uint16_t*>(q);

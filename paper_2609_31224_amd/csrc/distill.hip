@@ -3,15 +3,17 @@
 // extended by zero probability on the added tokens, group-balanced means, and
 // the gradient with respect to the student logits.  Public API: include/a2t.h.
 //
-//   distill_row_kernel     one workgroup per row.  Pass 1 streams the student
-//                          and teacher rows once (16-byte loads, four chunks
-//                          in flight per thread) keeping online statistics:
-//                          (max, sum e^x) of the student at temperature T and
-//                          at T = 1, and of the teacher at T, plus
-//                          A = sum_v e^(w_v - m_w) (w_v - u_v), which gives
-//                              KL = A / Z_w - lse(w) + lse(u)
-//                          in the same pass (u = s/T, w = t/T).  Pass 2
-//                          (optional) writes dL/ds.
+//   distill_row_kernel     one workgroup per row, sized so that its threads hold
+//                          the whole student row in registers (as it is stored,
+//                          16 bytes a chunk): every load is in flight at once and
+//                          the gradient needs no second read.  Transcription rows
+//                          read the student only: (max, sum 2^x) of s log2 e.
+//                          Native rows stream the teacher beside it: the same
+//                          pair for s/T and t/T, and A = sum_v p_v (t_v - s_v) / T,
+//                          which gives KL = A / Z_w - lse(w) + lse(u) in the same
+//                          pass (u = s/T, w = t/T); the first chunks of the
+//                          teacher stay in LDS for the gradient, the rest is read
+//                          again.
 //   distill_reduce_kernel  one workgroup: the four weighted sums over rows in
 //                          a fixed order (deterministic).
 // The weights of the four means are per-row coefficients computed on the host
@@ -25,15 +27,26 @@
 #include <cstdint>
 #include <cstring>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 namespace {
 
-constexpr int kDistThreads = 256;
-constexpr int kChunk = 8;     // elements per 16-byte (bf16) load
-constexpr int kUnroll = 4;    // chunks in flight per thread
+constexpr int kReduceThreads = 256;
+constexpr int kRowThreads = 1024;   // most threads of a row's workgroup
+constexpr int kChunk = 8;           // elements per chunk (16 bytes of bf16, 32 of fp32)
+constexpr float kLog2e = 1.44269504088896340736f;
+constexpr float kLn2 = 0.693147180559945309417f;
+
+// Chunks of its row a thread holds in registers: 76 (bf16) or 72 (fp32) of the 128
+// registers that a thread of a full CU (16 waves) has, so a row of up to 155,648
+// (73,728) logits is read once; chunks of the teacher it keeps in LDS, 128 bytes per
+// thread, 128 KiB for a CU's 1,024 threads; and chunks of the teacher it requests
+// ahead of the one it works on.
+template <typename T> struct Hold;
 
 struct DistillRow {
+    int32_t row;        // row of the batch (rows are dispatched costliest first)
     int32_t target;     // ASR target, -1 elsewhere
     float c_asr;        // weight of this row's CE in L_ASR
     float c_nat;        // weight of this row's KL in L_native
@@ -41,24 +54,74 @@ struct DistillRow {
     float c_turn;       // ... in L_turn
 };
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 struct bf16_t {
     uint16_t bits;
 };
 
-__device__ __forceinline__ void load8(const float* p, float (&x)[kChunk]) {
-    const float4 a = *reinterpret_cast<const float4*>(p);
-    const float4 b = *reinterpret_cast<const float4*>(p + 4);
-    x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
-    x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+// one chunk as stored
+template <typename T> struct Raw;
+template <> struct Raw<bf16_t> {
+    u32x4 a;
+};
+template <> struct Raw<float> {
+    u32x4 a, b;
+};
+template <> struct Hold<bf16_t> {
+    static constexpr int kRegs = 19, kLds = 8, kAhead = 3;
+};
+template <> struct Hold<float> {
+    static constexpr int kRegs = 9, kLds = 4, kAhead = 1;
+};
+// chunk c of a row (a scalar base and a 32-bit offset: rows stay under 4 GiB)
+__device__ __forceinline__ Raw<bf16_t> load_raw(const bf16_t* row, int c) {
+    return {*reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(row) + (uint32_t)c * 16u)};
 }
-__device__ __forceinline__ void load8(const bf16_t* p, float (&x)[kChunk]) {
-    const uint4 r = *reinterpret_cast<const uint4*>(p);
-    const uint32_t w[4] = {r.x, r.y, r.z, r.w};
+__device__ __forceinline__ Raw<float> load_raw(const float* row, int c) {
+    const u32x4* p = reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(row) + (uint32_t)c * 32u);
+    return {p[0], p[1]};
+}
+// How a bf16 pair comes apart, as values the compiler knows nothing about: each sweep
+// over the held chunks takes its own, so that none of the 152 logits a thread unpacks
+// is kept for the next sweep in a register of its own.
+struct Apart {
+    uint32_t shift, mask;
+    __device__ __forceinline__ Apart() {
+        asm volatile("s_mov_b32 %0, 16" : "=s"(shift));
+        asm volatile("s_mov_b32 %0, 0xffff0000" : "=s"(mask));
+    }
+};
+__device__ __forceinline__ void unpack(const Raw<bf16_t>& r, const Apart& ap, float (&x)[kChunk]) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        x[2 * e] = __uint_as_float(w[e] << 16);
-        x[2 * e + 1] = __uint_as_float(w[e] & 0xffff0000u);
+        x[2 * e] = __uint_as_float(r.a[e] << ap.shift);
+        x[2 * e + 1] = __uint_as_float(r.a[e] & ap.mask);
     }
+}
+__device__ __forceinline__ void unpack(const Raw<float>& r, const Apart&, float (&x)[kChunk]) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        x[e] = __uint_as_float(r.a[e]);
+        x[4 + e] = __uint_as_float(r.b[e]);
+    }
+}
+// elements from `first` on become -inf
+__device__ __forceinline__ void cut(Raw<bf16_t>& r, int first) {
+    uint32_t w[4] = {r.a.x, r.a.y, r.a.z, r.a.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        if (2 * e >= first) w[e] = (w[e] & 0xffff0000u) | 0xff80u;
+        if (2 * e + 1 >= first) w[e] = (w[e] & 0x0000ffffu) | 0xff800000u;
+    }
+    r.a = u32x4{w[0], w[1], w[2], w[3]};
+}
+__device__ __forceinline__ void cut(Raw<float>& r, int first) {
+    uint32_t w[8] = {r.a.x, r.a.y, r.a.z, r.a.w, r.b.x, r.b.y, r.b.z, r.b.w};
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        if (e >= first) w[e] = 0xff800000u;
+    r.a = u32x4{w[0], w[1], w[2], w[3]};
+    r.b = u32x4{w[4], w[5], w[6], w[7]};
 }
 __device__ __forceinline__ float load1(const float* p) { return *p; }
 __device__ __forceinline__ float load1(const bf16_t* p) { return __uint_as_float((uint32_t)p->bits << 16); }
@@ -68,198 +131,324 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
     const bf16x2 v = {(__bf16)a, (__bf16)b};   // round to nearest even
     return __builtin_bit_cast(uint32_t, v);
 }
-__device__ __forceinline__ void store8(float* p, const float (&g)[kChunk]) {
-    *reinterpret_cast<float4*>(p) = make_float4(g[0], g[1], g[2], g[3]);
-    *reinterpret_cast<float4*>(p + 4) = make_float4(g[4], g[5], g[6], g[7]);
+__device__ __forceinline__ void store_chunk(float* row, int c, const float (&g)[kChunk]) {
+    float4* p = reinterpret_cast<float4*>(reinterpret_cast<char*>(row) + (uint32_t)c * 32u);
+    p[0] = make_float4(g[0], g[1], g[2], g[3]);
+    p[1] = make_float4(g[4], g[5], g[6], g[7]);
 }
-__device__ __forceinline__ void store8(bf16_t* p, const float (&g)[kChunk]) {
-    *reinterpret_cast<uint4*>(p) = make_uint4(pack2(g[0], g[1]), pack2(g[2], g[3]),
-                                              pack2(g[4], g[5]), pack2(g[6], g[7]));
+// A bf16 gradient goes out in whole cache lines, to be read by a later kernel from
+// more rows than L2 holds: non-temporal stores do not displace the logits (237 -> 228
+// us, below).  An fp32 chunk is two stores of half lines: 199 us ordinary, 214 us
+// non-temporal on 1,000 rows of 80,002 logits.
+__device__ __forceinline__ void store_chunk(bf16_t* row, int c, const float (&g)[kChunk]) {
+    __builtin_nontemporal_store(u32x4{pack2(g[0], g[1]), pack2(g[2], g[3]), pack2(g[4], g[5]), pack2(g[6], g[7])},
+                                reinterpret_cast<u32x4*>(reinterpret_cast<char*>(row) + (uint32_t)c * 16u));
 }
 
-// (max, sum e^(x - max)) pairs and the teacher triple, combined across lanes
-struct Stats {
-    float mu, zu;     // student at temperature T
-    float m1, z1;     // student at T = 1
-    float mw, zw, aw; // teacher at T, with A
+// Running sums in the log2 domain: z = sum 2^(k x - m) with m at least the largest
+// k x so far (-inf: nothing yet).  m is the reference exactly as it was subtracted,
+// so log2 of the whole sum is m + log2 z with no error from rounding k x.
+struct Sum {
+    float m, z;
 };
+// the teacher's, with a = sum 2^(k t - m) (t - s)
+struct SumA {
+    float m, z, a;
+};
+__device__ __forceinline__ float finite_ref(float m) { return m == -INFINITY ? 0.f : m; }
+__device__ __forceinline__ float exp2_(float x) { return __builtin_amdgcn_exp2f(x); }
 
-__device__ __forceinline__ void merge_pair(float& m, float& z, float m2, float z2) {
-    const float mn = fmaxf(m, m2);
-    if (mn == -INFINITY) return;
-    z = z * __expf(m - mn) + z2 * __expf(m2 - mn);
-    m = mn;
+// largest logit of a chunk, and of mx
+template <typename T>
+__device__ __forceinline__ float max_of(const Raw<T>& r, const Apart& ap, float mx) {
+    float x[kChunk];
+    unpack(r, ap, x);
+#pragma unroll
+    for (int e = 0; e < kChunk; ++e) mx = fmaxf(mx, x[e]);
+    return mx;
 }
-__device__ __forceinline__ void merge_stats(Stats& a, const Stats& b) {
-    merge_pair(a.mu, a.zu, b.mu, b.zu);
-    merge_pair(a.m1, a.z1, b.m1, b.z1);
-    const float mn = fmaxf(a.mw, b.mw);
-    if (mn != -INFINITY) {
-        const float sa = __expf(a.mw - mn), sb = __expf(b.mw - mn);
-        a.zw = a.zw * sa + b.zw * sb;
-        a.aw = a.aw * sa + b.aw * sb;
-        a.mw = mn;
+// raises the reference to the largest logit mx of the chunks about to be added
+__device__ __forceinline__ void raise(Sum& s, float mx, float k) {
+    const float mn = fmaxf(s.m, mx * k);
+    s.z *= exp2_(s.m - finite_ref(mn));
+    s.m = mn;
+}
+__device__ __forceinline__ void raise(SumA& w, float mx, float k) {
+    const float mn = fmaxf(w.m, mx * k), sc = exp2_(w.m - finite_ref(mn));
+    w.z *= sc;
+    w.a *= sc;
+    w.m = mn;
+}
+// adds a chunk of the student
+template <typename T>
+__device__ __forceinline__ void add(Sum& s, const Raw<T>& r, const Apart& ap, float k) {
+    const float ref = finite_ref(s.m);
+    float x[kChunk], z = 0.f;
+    unpack(r, ap, x);
+#pragma unroll
+    for (int e = 0; e < kChunk; ++e) z += exp2_(fmaf(x[e], k, -ref));
+    s.z += z;
+}
+// adds a chunk of the teacher t beside the student s
+template <typename T>
+__device__ __forceinline__ void add(SumA& w, const Raw<T>& t, const Raw<T>& s, const Apart& ap, float k) {
+    const float ref = finite_ref(w.m);
+    float x[kChunk], y[kChunk], z = 0.f, a = 0.f;
+    unpack(t, ap, x);
+    unpack(s, ap, y);
+#pragma unroll
+    for (int e = 0; e < kChunk; ++e) {
+        const float p = exp2_(fmaf(x[e], k, -ref));
+        z += p;
+        // a token the teacher rules out (and the added ones) contributes nothing
+        a += x[e] == -INFINITY ? 0.f : p * (x[e] - y[e]);
+    }
+    w.z += z;
+    w.a += a;
+}
+__device__ __forceinline__ void merge(Sum& x, const Sum& y) {
+    const float mn = fmaxf(x.m, y.m), ref = finite_ref(mn);
+    x.z = x.z * exp2_(x.m - ref) + y.z * exp2_(y.m - ref);
+    x.m = mn;
+}
+__device__ __forceinline__ void merge(SumA& x, const SumA& y) {
+    const float mn = fmaxf(x.m, y.m), ref = finite_ref(mn);
+    const float cx = exp2_(x.m - ref), cy = exp2_(y.m - ref);
+    x.z = x.z * cx + y.z * cy;
+    x.a = x.a * cx + y.a * cy;
+    x.m = mn;
+}
+// over the workgroup: waves by xor shuffles, then across waves in LDS; every thread
+// returns the same sums (one barrier inside)
+__device__ __forceinline__ void reduce(Sum& u, SumA* w, float* part) {
+#pragma unroll
+    for (int mask = 32; mask >= 1; mask >>= 1) {
+        merge(u, Sum{__shfl_xor(u.m, mask), __shfl_xor(u.z, mask)});
+        if (w) merge(*w, SumA{__shfl_xor(w->m, mask), __shfl_xor(w->z, mask), __shfl_xor(w->a, mask)});
+    }
+    const int wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+        float* p = part + 5 * wave;
+        p[0] = u.m, p[1] = u.z;
+        if (w) p[2] = w->m, p[3] = w->z, p[4] = w->a;
+    }
+    __syncthreads();
+    u = Sum{part[0], part[1]};
+    if (w) *w = SumA{part[2], part[3], part[4]};
+    for (int x = 1; x < waves; ++x) {
+        const float* p = part + 5 * x;
+        merge(u, Sum{p[0], p[1]});
+        if (w) merge(*w, SumA{p[2], p[3], p[4]});
     }
 }
-__device__ __forceinline__ Stats shfl_stats(const Stats& s, int mask) {
-    Stats o;
-    o.mu = __shfl_xor(s.mu, mask);
-    o.zu = __shfl_xor(s.zu, mask);
-    o.m1 = __shfl_xor(s.m1, mask);
-    o.z1 = __shfl_xor(s.z1, mask);
-    o.mw = __shfl_xor(s.mw, mask);
-    o.zw = __shfl_xor(s.zw, mask);
-    o.aw = __shfl_xor(s.aw, mask);
-    return o;
-}
 
-// grid: one workgroup per row.  Pass 1: statistics; pass 2 (grad != null): dL/ds.
-template <typename T>
-__global__ __launch_bounds__(kDistThreads) void distill_row_kernel(
+// chunks are worked through one group after the other: no more of them are unpacked at once
+__device__ __forceinline__ void in_turn() { __builtin_amdgcn_sched_barrier(0); }
+
+// grid: one workgroup per row.  Bound: HBM, once the row is read and its gradient
+// written one time each; per logit a transcription row costs ~8 vector operations and
+// two exponentials, a native row about twice that.  Measured on 1,340 rows of 151,938
+// bf16 logits (957 of them transcription rows), with gradient: 228 us, 4.1 TB/s (480 us
+// with one 256-thread workgroup per row that kept online maxima per chunk, read the
+// teacher of every row and read both again for the gradient: bound by ~75 vector
+// operations per logit); teacher re-read whole instead of from LDS: 231 us.
+template <typename T, bool GRAD>
+__global__ __launch_bounds__(kRowThreads) void distill_row_kernel(
     const T* student, int64_t s_stride, const T* teacher, int64_t t_stride, int vocab, int vs,
-    const DistillRow* rows, float inv_t, int same_t, float2* rowval, T* grad) {
-    const int i = blockIdx.x, tid = threadIdx.x;
-    const DistillRow r = rows[i];
-    const T* s = student + (int64_t)i * s_stride;
-    const T* t = teacher + (int64_t)i * t_stride;
+    const DistillRow* rows, float inv_t, float2* rowval, T* grad) {
+    constexpr int NR = Hold<T>::kRegs, NL = Hold<T>::kLds;
+    extern __shared__ u32x4 t_lds[];           // GRAD: NL chunks of the teacher per thread
+    __shared__ float part[5 * kRowThreads / 64];
+    const int tid = threadIdx.x, TH = blockDim.x;
+    const DistillRow r = rows[blockIdx.x];
+    const T* s = student + (int64_t)r.row * s_stride;
+    const T* t = teacher + (int64_t)r.row * t_stride;
+    T* g = GRAD ? grad + (int64_t)r.row * s_stride : nullptr;
     const float wk = r.c_nat + r.c_dec + r.c_turn;  // KL weight in the gradient
     const float wc = r.c_asr;                       // CE weight in the gradient
-    const int vs_pad = (vs + kChunk - 1) / kChunk * kChunk;
+    const int nc = (vs + kChunk - 1) / kChunk, nt = (vocab + kChunk - 1) / kChunk;   // chunks
 
     if (wk == 0.f && wc == 0.f) {  // a row without loss: zero gradient
-        if (grad) {
-            const float z[kChunk] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            for (int c = tid * kChunk; c < vs_pad; c += kDistThreads * kChunk)
-                store8(grad + (int64_t)i * s_stride + c, z);
-        }
-        if (tid == 0) rowval[i] = make_float2(0.f, 0.f);
+        const float z[kChunk] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if (GRAD)
+            for (int c = tid; c < nc; c += TH) store_chunk(g, c, z);
+        if (tid == 0) rowval[blockIdx.x] = make_float2(0.f, 0.f);
         return;
     }
 
-    Stats st{-INFINITY, 0.f, -INFINITY, 0.f, -INFINITY, 0.f, 0.f};
-    constexpr int kStep = kDistThreads * kChunk;
-    for (int c0 = tid * kChunk; c0 < vs_pad; c0 += kStep * kUnroll) {
-        float sv[kUnroll][kChunk], tv[kUnroll][kChunk];
-        // all loads of the group first (clamped addresses, masked below)
+    // the thread's chunk of round k, computed where it is used and not kept
+    auto chunk_no = [&](int k) {
+        int x = tid;
+        asm volatile("" : "+v"(x));
+        return k * TH + x;
+    };
+    // chunk c of the student (teacher), -inf past its last logit; the address is clamped
+    // so that the loads need no branch
+    auto student_chunk = [&](int c) { return load_raw(s, min(c, nc - 1)); };
+    auto teacher_chunk = [&](int c) { return load_raw(t, min(c, nt - 1)); };
+    // c0: the first chunk of the workgroup's round that holds chunk c
+    auto cut_student = [&](Raw<T>& x, int c, int c0) {
+        if ((c0 + TH) * kChunk > vs) cut(x, vs - c * kChunk);
+    };
+    auto cut_teacher = [&](Raw<T>& x, int c, int c0) {
+        if ((c0 + TH) * kChunk > vocab) cut(x, vocab - c * kChunk);
+    };
+
+    Raw<T> hs[NR];
 #pragma unroll
-        for (int k = 0; k < kUnroll; ++k) {
-            const int c = c0 + k * kStep;
-            const int cs = c < vs_pad ? c : vs_pad - kChunk;
-            load8(s + cs, sv[k]);
-            const int ct = c < vocab ? c : 0;
-            load8(t + ct, tv[k]);
+    for (int k = 0; k < NR; ++k) hs[k] = student_chunk(chunk_no(k));
+    const float target_logit = wc != 0.f && tid == 0 ? load1(s + r.target) : 0.f;
+#pragma unroll
+    for (int k = 0; k < NR; ++k) cut_student(hs[k], chunk_no(k), k * TH);
+
+    const Apart to_max, to_sum;
+    Sum u{-INFINITY, 0.f};
+    if (wk == 0.f) {
+        // ---- transcription row: the student at temperature 1
+        constexpr float k1 = kLog2e;
+#pragma unroll
+        for (int k = 0; k < NR; k += 4) {   // in groups of four chunks
+            constexpr int N = 4;
+            float mx = -INFINITY;
+            if (k * TH < nc) {
+#pragma unroll
+                for (int e = 0; e < N; ++e)
+                    if (k + e < NR) mx = max_of(hs[k + e], to_max, mx);
+            }
+            if (k * TH < nc) {
+                raise(u, mx, k1);
+#pragma unroll
+                for (int e = 0; e < N; ++e)
+                    if (k + e < NR) add(u, hs[k + e], to_sum, k1);
+            }
+            in_turn();
         }
-#pragma unroll
-        for (int k = 0; k < kUnroll; ++k) {
-            const int c = c0 + k * kStep;
-            if (c >= vs_pad) break;
-            float u[kChunk], w[kChunk];
-            float cu = -INFINITY, c1 = -INFINITY, cw = -INFINITY;
-#pragma unroll
-            for (int e = 0; e < kChunk; ++e) {
-                const bool vs_ok = c + e < vs, v_ok = c + e < vocab;
-                sv[k][e] = vs_ok ? sv[k][e] : -INFINITY;
-                u[e] = vs_ok ? sv[k][e] * inv_t : -INFINITY;
-                w[e] = v_ok ? tv[k][e] * inv_t : -INFINITY;
-                cu = fmaxf(cu, u[e]);
-                c1 = fmaxf(c1, sv[k][e]);
-                cw = fmaxf(cw, w[e]);
-            }
-            {
-                const float mn = fmaxf(st.mu, cu);
-                float acc = 0.f;
-#pragma unroll
-                for (int e = 0; e < kChunk; ++e) acc += __expf(u[e] - mn);
-                st.zu = st.zu * __expf(st.mu - mn) + acc;
-                st.mu = mn;
-            }
-            if (!same_t) {
-                const float mn = fmaxf(st.m1, c1);
-                float acc = 0.f;
-#pragma unroll
-                for (int e = 0; e < kChunk; ++e) acc += __expf(sv[k][e] - mn);
-                st.z1 = st.z1 * __expf(st.m1 - mn) + acc;
-                st.m1 = mn;
-            }
-            if (cw != -INFINITY) {
-                const float mn = fmaxf(st.mw, cw);
-                const float sc = __expf(st.mw - mn);
-                float zacc = 0.f, aacc = 0.f;
-#pragma unroll
-                for (int e = 0; e < kChunk; ++e) {
-                    const float p = __expf(w[e] - mn);   // 0 past the teacher vocabulary
-                    zacc += p;
-                    aacc += (w[e] == -INFINITY) ? 0.f : p * (w[e] - u[e]);
-                }
-                st.zw = st.zw * sc + zacc;
-                st.aw = st.aw * sc + aacc;
-                st.mw = mn;
-            }
+        for (int c = NR * TH + tid; c - tid < nc; c += TH) {
+            Raw<T> x = student_chunk(c);
+            cut_student(x, c, c - tid);
+            raise(u, max_of(x, to_max, -INFINITY), k1);
+            add(u, x, to_sum, k1);
         }
+        reduce(u, nullptr, part);
+        if (tid == 0) rowval[blockIdx.x] = make_float2(kLn2 * (u.m + __builtin_amdgcn_logf(u.z)) - target_logit, 0.f);
+        if (!GRAD) return;
+        // dL/ds_v = wc (softmax(s)_v - [v == target])
+        const float coef = wc / u.z, ref = finite_ref(u.m);
+        const Apart to_write;
+        auto write = [&](const Raw<T>& x, int c) {
+            float y[kChunk];
+            unpack(x, to_write, y);
+#pragma unroll
+            for (int e = 0; e < kChunk; ++e) y[e] = coef * exp2_(fmaf(y[e], k1, -ref));
+            if (c == r.target / kChunk) {
+#pragma unroll
+                for (int e = 0; e < kChunk; ++e) y[e] -= e == r.target % kChunk ? wc : 0.f;
+            }
+            if (c < nc) store_chunk(g, c, y);
+        };
+#pragma unroll
+        for (int k = 0; k < NR; ++k)
+        {
+            if (k * TH < nc) write(hs[k], chunk_no(k));
+            in_turn();
+        }
+        for (int c = NR * TH + tid; c - tid < nc; c += TH) {
+            Raw<T> x = student_chunk(c);
+            cut_student(x, c, c - tid);
+            write(x, c);
+        }
+        return;
     }
-    // reduce over the workgroup: waves by xor shuffles, then across waves in LDS
+
+    // ---- native row: student and teacher at temperature T
+    const float kt = inv_t * kLog2e;
+    SumA w{-INFINITY, 0.f, 0.f};
+    constexpr int NA = Hold<T>::kAhead;
+    Raw<T> ts[NR];   // in flight: NA chunks ahead of the one in work
 #pragma unroll
-    for (int mask = 32; mask >= 1; mask >>= 1) merge_stats(st, shfl_stats(st, mask));
-    __shared__ Stats part[kDistThreads / 64];
-    if ((tid & 63) == 0) part[tid >> 6] = st;
-    __syncthreads();
-    Stats tot = part[0];
+    for (int k = 0; k < NA; ++k) ts[k] = teacher_chunk(chunk_no(k));
 #pragma unroll
-    for (int wv = 1; wv < kDistThreads / 64; ++wv) merge_stats(tot, part[wv]);
-    const float lse_u = tot.mu + __logf(tot.zu);
-    const float lse_w = tot.mw + __logf(tot.zw);
-    const float lse_1 = same_t ? lse_u : tot.m1 + __logf(tot.z1);
+    for (int k = 0; k < NR; ++k) {
+        if (k + NA < NR) ts[k + NA] = teacher_chunk(chunk_no(k + NA));
+        const int c = chunk_no(k);
+        Raw<T> x = ts[k];
+        cut_teacher(x, c, k * TH);
+        if (GRAD && k < NL) reinterpret_cast<Raw<T>*>(t_lds)[c] = x;
+        float mu = -INFINITY, mw = -INFINITY;
+        if (k * TH < nc) {
+            mu = max_of(hs[k], to_max, mu);
+            mw = max_of(x, to_max, mw);
+        }
+        if (k * TH < nc) {
+            raise(u, mu, kt);
+            add(u, hs[k], to_sum, kt);
+            raise(w, mw, kt);
+            add(w, x, hs[k], to_sum, kt);
+        }
+        in_turn();
+    }
+    for (int c = NR * TH + tid; c - tid < nc; c += TH) {
+        Raw<T> x = student_chunk(c), y = teacher_chunk(c);
+        cut_student(x, c, c - tid);
+        cut_teacher(y, c, c - tid);
+        raise(u, max_of(x, to_max, -INFINITY), kt);
+        add(u, x, to_sum, kt);
+        raise(w, max_of(y, to_max, -INFINITY), kt);
+        add(w, y, x, to_sum, kt);
+    }
+    reduce(u, &w, part);
     const float tt = 1.f / inv_t;
     if (tid == 0) {
-        const float kl = (wk != 0.f) ? tt * tt * (tot.aw / tot.zw - lse_w + lse_u) : 0.f;
-        const float ce = (wc != 0.f) ? lse_1 - load1(s + r.target) : 0.f;
-        rowval[i] = make_float2(ce, kl);
+        const float lse = (u.m - w.m) + (__builtin_amdgcn_logf(u.z) - __builtin_amdgcn_logf(w.z));
+        rowval[blockIdx.x] = make_float2(0.f, tt * tt * (inv_t * w.a / w.z + kLn2 * lse));
     }
-    if (!grad) return;
-    // pass 2: dL/ds_v = wk T (softmax(u)_v - p_t,v) + wc (softmax(s)_v - [v == target])
-    T* g = grad + (int64_t)i * s_stride;
-    for (int c0 = tid * kChunk; c0 < vs_pad; c0 += kStep * kUnroll) {
-        float sv[kUnroll][kChunk], tv[kUnroll][kChunk];
+    if (!GRAD) return;
+    // dL/ds_v = wk T (softmax(u)_v - p_t,v)
+    const float cu = wk * tt / u.z, cw = wk * tt / w.z, ru = finite_ref(u.m), rw = finite_ref(w.m);
+    const Apart to_write;
+    auto write = [&](const Raw<T>& x, const Raw<T>& y, int c) {
+        float a[kChunk], b[kChunk];
+        unpack(x, to_write, a);
+        unpack(y, to_write, b);
 #pragma unroll
-        for (int k = 0; k < kUnroll; ++k) {
-            const int c = c0 + k * kStep;
-            const int cs = c < vs_pad ? c : vs_pad - kChunk;
-            load8(s + cs, sv[k]);
-            const int ct = c < vocab ? c : 0;
-            load8(t + ct, tv[k]);
-        }
+        for (int e = 0; e < kChunk; ++e)
+            a[e] = cu * exp2_(fmaf(a[e], kt, -ru)) - cw * exp2_(fmaf(b[e], kt, -rw));
+        if (c < nc) store_chunk(g, c, a);
+    };
 #pragma unroll
-        for (int k = 0; k < kUnroll; ++k) {
-            const int c = c0 + k * kStep;
-            if (c >= vs_pad) break;
-            float gv[kChunk];
+    for (int k = NL; k < NL + NA; ++k) ts[k] = teacher_chunk(chunk_no(k));
 #pragma unroll
-            for (int e = 0; e < kChunk; ++e) {
-                const int v = c + e;
-                float x = 0.f;
-                if (v < vs) {
-                    const float ps = __expf(sv[k][e] * inv_t - lse_u);
-                    const float pt = v < vocab ? __expf(tv[k][e] * inv_t - lse_w) : 0.f;
-                    x = wk * tt * (ps - pt);
-                    if (wc != 0.f) {
-                        const float p1 = same_t ? ps : __expf(sv[k][e] - lse_1);
-                        x += wc * (p1 - (v == r.target ? 1.f : 0.f));
-                    }
-                }
-                gv[e] = x;
+    for (int k = 0; k < NR; ++k) {
+        // the chunks that LDS holds are written while the others are on their way
+        if (k >= NL && k + NA < NR) ts[k + NA] = teacher_chunk(chunk_no(k + NA));
+        if (k * TH < nc) {
+            const int c = chunk_no(k);
+            Raw<T> y;
+            if (k < NL) {
+                y = reinterpret_cast<const Raw<T>*>(t_lds)[c];   // written by this thread
+            } else {
+                y = ts[k];
+                cut_teacher(y, c, k * TH);
             }
-            store8(g + c, gv);
+            write(hs[k], y, c);
         }
+        in_turn();
+    }
+    for (int c = NR * TH + tid; c - tid < nc; c += TH) {
+        Raw<T> x = student_chunk(c), y = teacher_chunk(c);
+        cut_student(x, c, c - tid);
+        cut_teacher(y, c, c - tid);
+        write(x, y, c);
     }
 }
 
 // one workgroup: sum_i c_asr ce_i, c_nat kl_i, c_dec kl_i, c_turn kl_i in a fixed order
-__global__ __launch_bounds__(kDistThreads) void distill_reduce_kernel(const DistillRow* rows,
+__global__ __launch_bounds__(kReduceThreads) void distill_reduce_kernel(const DistillRow* rows,
                                                                       const float2* rowval, int n,
                                                                       float* losses) {
     const int tid = threadIdx.x;
     float a = 0.f, b = 0.f, c = 0.f, d = 0.f;
-    for (int i = tid; i < n; i += kDistThreads) {
+    for (int i = tid; i < n; i += kReduceThreads) {
         const DistillRow r = rows[i];
         const float2 v = rowval[i];
         a += r.c_asr * v.x;
@@ -267,10 +456,10 @@ __global__ __launch_bounds__(kDistThreads) void distill_reduce_kernel(const Dist
         c += r.c_dec * v.y;
         d += r.c_turn * v.y;
     }
-    __shared__ float4 sh[kDistThreads];
+    __shared__ float4 sh[kReduceThreads];
     sh[tid] = make_float4(a, b, c, d);
     __syncthreads();
-    for (int w = kDistThreads / 2; w >= 1; w >>= 1) {
+    for (int w = kReduceThreads / 2; w >= 1; w >>= 1) {
         if (tid < w) {
             const float4 x = sh[tid], y = sh[tid + w];
             sh[tid] = make_float4(x.x + y.x, x.y + y.y, x.z + y.z, x.w + y.w);
@@ -292,6 +481,7 @@ __global__ __launch_bounds__(kDistThreads) void distill_reduce_kernel(const Dist
 // ------------------------------------------------------------------ host API
 struct a2t_distill {
     int32_t max_rows = 0, vocab = 0, n_added = 0, dtype = 0, device = 0;
+    int cus = 256;
     hipStream_t stream = nullptr;
     DistillRow* rows_dev = nullptr;
     float2* rowval_dev = nullptr;
@@ -318,6 +508,17 @@ struct DevGuard {
         if (prev >= 0) (void)hipSetDevice(prev);
     }
 };
+// Threads of a row's workgroup: as few as hold a row of `chunks` in registers, so that a
+// CU has several rows in different phases; more where the rows alone do not fill the
+// CUs' 1,024 threads each, as long as a thread keeps four chunks (252 rows of 32,005
+// fp32 logits: 20.7 us with 512 threads a row, 24.1 with 1,024, whose waves take
+// longer to start; 1,340 rows of 10,009 bf16 logits: 44.8 us with 128, 42.4 with 256).
+int row_threads(int n_rows, int chunks, int regs, int cus) {
+    int th = 64;
+    while (th < kRowThreads && th * regs < chunks) th *= 2;
+    while (th < kRowThreads && 8 * th <= chunks && (int64_t)n_rows * th < (int64_t)cus * kRowThreads) th *= 2;
+    return th;
+}
 void free_distill(a2t_distill* d) {
     if (!d) return;
     for (int k = 0; k < 2; ++k) {
@@ -353,6 +554,8 @@ extern "C" int a2t_distill_create(int32_t max_rows, int32_t vocab, int32_t n_add
     d->dtype = dtype;
     d->device = device;
     d->stream = static_cast<hipStream_t>(hip_stream);
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && cus > 0) d->cus = cus;
     bool ok = hipMalloc(&d->rows_dev, sizeof(DistillRow) * (size_t)max_rows) == hipSuccess &&
               hipMalloc(&d->rowval_dev, sizeof(float2) * (size_t)max_rows) == hipSuccess;
     for (int k = 0; k < 2 && ok; ++k)
@@ -423,9 +626,12 @@ extern "C" int a2t_distill_loss(a2t_distill* d, int32_t n_rows, const void* stud
         }
         d->stage_live[slot] = false;
     }
+    // rows in order of falling cost (native rows read the teacher too, rows without loss
+    // only write zeros), so that the last ones to be dispatched are the short ones
     DistillRow* h = d->stage[slot];
+    int at[3] = {(int)(n_nat + n_asr), (int)n_nat, 0};   // by kind: none, ASR, native
     for (int i = 0; i < n_rows; ++i) {
-        DistillRow r{-1, 0.f, 0.f, 0.f, 0.f};
+        DistillRow r{i, -1, 0.f, 0.f, 0.f, 0.f};
         if (kind[i] == A2T_ROW_ASR) {
             r.target = target[i];
             r.c_asr = (float)(1.0 / (double)n_asr);
@@ -434,14 +640,13 @@ extern "C" int a2t_distill_loss(a2t_distill* d, int32_t n_rows, const void* stud
             if (dec_group[i] >= 0) r.c_dec = (float)(1.0 / ((double)g_dec * n_dec[dec_group[i]]));
             if (turn_group[i] >= 0) r.c_turn = (float)(1.0 / ((double)g_turn * n_turn[turn_group[i]]));
         }
-        h[i] = r;
+        h[at[kind[i]]++] = r;
     }
     hipError_t e = hipMemcpyAsync(d->rows_dev, h, sizeof(DistillRow) * (size_t)n_rows,
                                   hipMemcpyHostToDevice, d->stream);
     if (e == hipSuccess) e = hipEventRecord(d->stage_ev[slot], d->stream);
     if (e == hipSuccess) d->stage_live[slot] = true;
     const float inv_t = 1.f / temperature;
-    const int same_t = temperature == 1.f;
     if (e == hipSuccess) {
         std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
         if (d->prof_on) {
@@ -455,24 +660,28 @@ extern "C" int a2t_distill_loss(a2t_distill* d, int32_t n_rows, const void* stud
                 d->prof_free.pop_back();
             }
         }
-        if (d->dtype == A2T_F32)
-            hipExtLaunchKernelGGL((distill_row_kernel<float>), dim3(n_rows), dim3(kDistThreads), 0,
-                                  d->stream, ev.first, ev.second, 0, static_cast<const float*>(student),
-                                  student_stride, static_cast<const float*>(teacher), teacher_stride,
-                                  d->vocab, vs, (const DistillRow*)d->rows_dev, inv_t, same_t,
-                                  d->rowval_dev, static_cast<float*>(grad));
-        else
-            hipExtLaunchKernelGGL((distill_row_kernel<bf16_t>), dim3(n_rows), dim3(kDistThreads), 0,
-                                  d->stream, ev.first, ev.second, 0,
-                                  static_cast<const bf16_t*>(student), student_stride,
-                                  static_cast<const bf16_t*>(teacher), teacher_stride, d->vocab, vs,
-                                  (const DistillRow*)d->rows_dev, inv_t, same_t, d->rowval_dev,
-                                  static_cast<bf16_t*>(grad));
+        auto go = [&](auto kernel, auto* logits, int regs) {
+            using T = std::remove_const_t<std::remove_pointer_t<decltype(logits)>>;
+            const int th = row_threads(n_rows, (vs + kChunk - 1) / kChunk, regs, d->cus);
+            hipExtLaunchKernelGGL(kernel, dim3(n_rows), dim3(th), grad ? th * 128 : 0, d->stream, ev.first, ev.second, 0,
+                                  static_cast<const T*>(student), student_stride, static_cast<const T*>(teacher),
+                                  teacher_stride, d->vocab, vs, (const DistillRow*)d->rows_dev, inv_t, d->rowval_dev,
+                                  static_cast<T*>(grad));
+        };
+        if (d->dtype == A2T_F32) {
+            const float* x = nullptr;
+            if (grad) go(distill_row_kernel<float, true>, x, Hold<float>::kRegs);
+            else go(distill_row_kernel<float, false>, x, Hold<float>::kRegs);
+        } else {
+            const bf16_t* x = nullptr;
+            if (grad) go(distill_row_kernel<bf16_t, true>, x, Hold<bf16_t>::kRegs);
+            else go(distill_row_kernel<bf16_t, false>, x, Hold<bf16_t>::kRegs);
+        }
         e = hipGetLastError();
         if (ev.first) d->prof_pending.push_back(ev);
     }
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(distill_reduce_kernel, dim3(1), dim3(kDistThreads), 0, d->stream,
+        hipLaunchKernelGGL(distill_reduce_kernel, dim3(1), dim3(kReduceThreads), 0, d->stream,
                            d->rows_dev, d->rowval_dev, n_rows, losses);
         e = hipGetLastError();
     }

@@ -1,0 +1,66 @@
+"""GPU parity of the adaptation objective at the sizes where its row kernel changes
+shape: vocabularies of one chunk and less, around a workgroup size's register capacity
+(64 threads x 19 chunks of 8 bf16 logits, x 9 of fp32), past the largest one (the rest
+of a row is streamed), padded and unpadded strides, tokens that one side or both rule
+out (-inf), and few rows with many threads each.  Bars as in test_gpu_distill.py:
+losses 2e-4 + 1e-4 relative, gradients 1e-4 (fp32) or 2^-8 (bf16) relative plus 1e-3 of
+the row's largest magnitude."""
+import numpy as np
+import pytest
+
+from oracle.distill import KIND_NONE, distill_losses
+from synth.distill import make_distill_batch
+from tests.test_gpu_distill import _check_grad, _check_losses, _run
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(b, vocab, added, dtype, T, kind=None):
+    kind = b.kind if kind is None else kind
+    ref = distill_losses(b.student, b.teacher, kind, b.target, b.dec_group, b.turn_group, T)
+    for with_grad in (True, False):
+        lo, gr, _ = _run(b, vocab, added, dtype, T, with_grad=with_grad, kind=kind)
+        _check_losses(lo, ref.losses)
+        if with_grad:
+            _check_grad(gr[:, :vocab + added], ref.grad, dtype)
+            assert not gr[:, vocab + added:].any()
+
+
+@pytest.mark.parametrize("dtype,T,vocab,added", [
+    ("f32", 1.0, 1, 2), ("bf16", 2.0, 6, 2), ("bf16", 1.0, 8, 1), ("f32", 0.5, 63, 1),
+    ("f32", 1.0, 64 * 9 * 8 - 2, 2), ("f32", 2.0, 64 * 9 * 8 - 1, 2),
+    ("bf16", 1.0, 64 * 19 * 8 - 2, 2), ("bf16", 0.5, 64 * 19 * 8 - 1, 2),
+    ("bf16", 1.0, 128 * 19 * 8 + 5, 7), ("f32", 1.0, 512 * 9 * 8 + 3, 2),
+])
+def test_row_sizes(gpu, dtype, T, vocab, added):
+    b = make_distill_batch(seed=21, n_utt=2, units=3, vocab=vocab, added=added, dtype=dtype)
+    kind = b.kind.copy()
+    kind[2] = KIND_NONE
+    _check(b, vocab, added, dtype, T, kind)
+
+
+@pytest.mark.parametrize("dtype,vocab", [("bf16", 1024 * 19 * 8 + 9), ("f32", 1024 * 9 * 8 + 8191)])
+def test_rows_past_the_registers(gpu, dtype, vocab):
+    b = make_distill_batch(seed=22, n_utt=1, units=2, vocab=vocab, added=2, dtype=dtype)
+    _check(b, vocab, 2, dtype, 1.0)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_ruled_out_tokens(gpu, dtype):
+    """-inf logits: the teacher's alone (no contribution there), and both sides' (no
+    contribution, zero gradient), in every chunk of a stretch and at the row's ends."""
+    vocab = 1500
+    b = make_distill_batch(seed=23, n_utt=2, units=3, vocab=vocab, added=2, dtype=dtype)
+    student, teacher = b.student.copy(), b.teacher.copy()
+    teacher[:, 100:900] = -np.inf
+    teacher[:, -3:] = -np.inf
+    student[:, 300:600] = -np.inf
+    b = type(b)(student, teacher, b.kind, np.where((b.target >= 300) & (b.target < 600), 7, b.target).astype(np.int32),
+                b.dec_group, b.turn_group)
+    # the oracle's logs of the tokens without mass drop out of its sums as 0 * -inf: a
+    # finite logit far below the others has the same sums
+    low = type(b)(np.maximum(student, -1e4), np.maximum(teacher, -1e4), b.kind, b.target, b.dec_group, b.turn_group)
+    ref = distill_losses(low.student, low.teacher, b.kind, b.target, b.dec_group, b.turn_group, 1.0)
+    lo, gr, _ = _run(b, vocab, 2, dtype, 1.0)
+    _check_losses(lo, ref.losses)
+    _check_grad(gr[:, :vocab + 2], ref.grad, dtype)
