@@ -175,7 +175,7 @@ typedef struct a2t_stream_info {
  *   A2T_TARGET_WGS  attention workgroups one launch spreads over (default:
  *                   the device's CU count, one 8-wave workgroup per CU)
  *   A2T_SPLITS      force this many key splits per stream (0 = planned)
- *   A2T_FORCE_VALU  nonzero: the VALU attention kernel for bf16 caches too */
+ *   A2T_FORCE_VALU  nonzero: the VALU attention kernel for bf16 caches */
 int a2t_cache_create(const a2t_config* cfg, void* hip_stream, a2t_cache** out);
 
 /* Wait for the stream, then free everything the cache owns.  NULL is a no-op. */
@@ -421,7 +421,7 @@ int a2t_sync(a2t_cache* c);
 /* Kernel timing with HIP events on the cache's stream (for benchmarks).
  * kernel_filter: NULL disables timing; "" times every kernel; otherwise only
  * kernels whose name contains the string ("step_meta", "append",
- * "attn_tile", "attn_valu", "attn_merge", "evict").  While enabled, each
+ * "attn_tile", "attn_block", "attn_f32", "attn_valu", "attn_merge", "evict").  While enabled, each
  * matching launch carries a start/stop event pair recorded at the dispatch's
  * own begin and end.  a2t_kernel_time waits for the
  * stream, then reports for the kernels whose name contains `kernel` the

@@ -17,7 +17,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libA2T.so")
-SOURCES = ["kernels.hip", "attn_block.hip", "a2t.cpp", "distill.hip"]
+SOURCES = ["kernels.hip", "attn_block.hip", "attn_f32.hip", "a2t.cpp", "distill.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

@@ -432,6 +432,42 @@ void plan_block_splits(const a2t_cache* c, int n, const int* tiles, const int32_
     std::fill(splits, splits + n, 1);
 }
 
+// Key splits and query blocks per workgroup of an attn_f32 launch.
+//
+// Two query blocks per workgroup halve the K and V that a launch fetches from L2 (2 streams
+// of ~2,100 keys, 88 query rows per KV head, 32/8 heads of 128: 26.5 against 31 us); one
+// where workgroups of two would leave most CUs idle (88 query rows of one KV head, 280 keys:
+// 9.5 against 12.6 us).
+// Streams of up to kF32WholeTiles tiles are not split: the merge costs more than the split
+// gains (the same 280 keys: 9.5 us against 7.6 + 3.9 with one).  Longer ones get the fewest
+// tiles per split (at least 2) whose workgroups fit one round over the CUs; two workgroups per
+// CU were slower (33 against 26.5 us).
+constexpr int kF32WholeTiles = 8;
+void plan_f32(const a2t_cache* c, int n, const int* tiles, const int32_t* n_q, const int64_t* floats_per_split,
+              int* splits, int* query_blocks, int64_t ws_limit) {
+    const int Hkv = c->cfg.n_kv_heads, G = c->cfg.n_q_heads / Hkv;
+    int max_tiles = 1, max_rows = 1;
+    int64_t pairs = 0;
+    for (int i = 0; i < n; ++i) {
+        max_tiles = std::max(max_tiles, tiles[i]);
+        max_rows = std::max(max_rows, G * n_q[i]);
+        pairs += (int64_t)Hkv * f32_groups(G * n_q[i], 2) * ((tiles[i] + kF32WholeTiles - 1) / kF32WholeTiles);
+    }
+    *query_blocks = max_rows > 16 && pairs * 2 >= c->target_wgs ? 2 : 1;
+    const bool force = c->force_splits > 0;
+    for (int budget = !force && max_tiles <= kF32WholeTiles ? max_tiles : std::min(2, max_tiles); budget <= max_tiles; ++budget) {
+        int64_t wgs = 0, ws = 0;
+        for (int i = 0; i < n; ++i) {
+            const int want = force ? std::min(c->force_splits, tiles[i]) : (tiles[i] + budget - 1) / budget;
+            splits[i] = std::max(1, std::min(want, kMaxSplits));
+            wgs += (int64_t)splits[i] * Hkv * f32_groups(G * n_q[i], *query_blocks);
+            ws += stream_partials(splits[i], floats_per_split[i]);
+        }
+        if ((wgs <= c->target_wgs || force) && ws <= ws_limit) return;
+    }
+    std::fill(splits, splits + n, 1);
+}
+
 // Where a launch's split partials go: the cache's workspace (default) or the
 // library's fixed device array (the no-allocation entry point, which plans
 // without the workspace limit and never times its launches).
@@ -477,8 +513,9 @@ int attn_launch(a2t_cache* c, int layer, int n, const int32_t* ids, const int32_
     // bf16 caches use the MFMA kernel for decode too: with one query row per
     // stream it is still bound by streaming the resident K/V, and its staged
     // tile pipeline keeps more bytes in flight than the VALU kernel.
-    const bool valu = c->cfg.dtype == A2T_F32 || c->force_valu;
-    const int64_t rf = partial_row_floats(c->cfg.head_dim, valu);
+    const bool f32 = c->cfg.dtype == A2T_F32, valu = !f32 && c->force_valu;
+    const int64_t rf = partial_row_floats(c->cfg.head_dim, f32 || valu);
+    int query_blocks = 1;
     int max_rows = 0, tiles[kMaxDesc], nsplit[kMaxDesc];
     int64_t floats[kMaxDesc];
     for (int i = 0; i < n; ++i) {
@@ -488,7 +525,9 @@ int attn_launch(a2t_cache* c, int layer, int n, const int32_t* ids, const int32_
         floats[i] = (int64_t)c->cfg.n_kv_heads * G * n_q[i] * rf;
     }
     const bool block = !in_row0 && many_rows(c, n, ids, n_q);
-    if (block)
+    if (f32)
+        plan_f32(c, n, tiles, n_q, floats, nsplit, &query_blocks, wsc ? wsc->floats : c->dev.ws_floats);
+    else if (block)
         plan_block_splits(c, n, tiles, n_q, floats, nsplit, wsc ? wsc->floats : c->dev.ws_floats);
     else
         plan_splits(c, n, tiles, floats, nsplit, wsc ? INT64_MAX : c->dev.ws_floats);
@@ -526,7 +565,7 @@ int attn_launch(a2t_cache* c, int layer, int n, const int32_t* ids, const int32_
     // per tile holding them) still fit one round over the CUs, those tiles get
     // one-tile splits of their own, so that the workgroup that also rotates and
     // stores the rows is not the last of the launch to finish
-    if (in_row0 && !wsc) {
+    if (in_row0 && !wsc && !f32) {
         const int Hkv = c->cfg.n_kv_heads;
         int64_t wgs = 0, ws = 0;
         int32_t tq[kMaxDesc], tr[kMaxDesc], ns[kMaxDesc];
@@ -565,6 +604,7 @@ int attn_launch(a2t_cache* c, int layer, int n, const int32_t* ids, const int32_
     b.max_rows = max_rows;
     hipError_t e;
     auto launch = [&](const DevState& st, const KTimer& kt) {
+        if (f32) return launch_attn_f32(st, b, query_blocks, q, o, k_in, v_in, c->stream, kt);
         if (valu) return launch_attn_valu(st, b, q, o, c->stream, kt);
         if (block) return launch_attn_block(st, b, q, o, c->stream, kt);
         return launch_attn_tile(st, b, q, o, k_in, v_in, c->stream, kt);
@@ -577,17 +617,17 @@ int attn_launch(a2t_cache* c, int layer, int n, const int32_t* ids, const int32_
         st.ws_floats = wsc->floats;
         const KTimer none{};
         e = launch(st, none);
-        if (e == hipSuccess && splits > 1) e = launch_attn_merge(st, b, o, c->stream, none, !valu);
+        if (e == hipSuccess && splits > 1) e = launch_attn_merge(st, b, o, c->stream, none, !(f32 || valu));
         return e == hipSuccess ? A2T_OK : hip_fail(c);
     }
     {
-        ProfScope ps(c, valu ? "attn_valu" : block ? "attn_block" : "attn_tile");
+        ProfScope ps(c, f32 ? "attn_f32" : valu ? "attn_valu" : block ? "attn_block" : "attn_tile");
         e = launch(c->dev, ps.kt());
     }
     if (e != hipSuccess) return hip_fail(c);
     if (splits > 1) {
         ProfScope ps(c, "attn_merge");
-        if (launch_attn_merge(c->dev, b, o, c->stream, ps.kt(), !valu) != hipSuccess) return hip_fail(c);
+        if (launch_attn_merge(c->dev, b, o, c->stream, ps.kt(), !(f32 || valu)) != hipSuccess) return hip_fail(c);
     }
     return A2T_OK;
 }
@@ -1018,7 +1058,7 @@ int append_attn_impl(a2t_cache* c, int32_t layer, int32_t n_streams, const int32
                      void* o, const WsChoice* wsc) {
     // steps of many query rows append first and then run attn_block: each of its
     // query blocks would otherwise rotate the step's keys again
-    bool fused = c->cfg.dtype == A2T_BF16 && !c->force_valu;
+    bool fused = c->cfg.dtype == A2T_F32 || !c->force_valu;
     for (int i0 = 0; i0 < n_streams && fused; i0 += kMaxDesc)
         fused = !many_rows(c, std::min(kMaxDesc, n_streams - i0), ids + i0, n_q + i0);
     int rc = append_impl(c, layer, n_streams, ids, n_rows, kin, vin, seg, pos, unit_id, !fused);

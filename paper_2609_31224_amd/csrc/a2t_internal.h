@@ -22,6 +22,9 @@ constexpr int kMaxSplits = 128;
 constexpr int kMergeRows = 4;
 // Query rows (G * n_q rows of a KV head) per workgroup of attn_block.
 constexpr int kBlockRows = 128;
+// Workgroups of attn_f32 (per split and KV head) that cover query_rows rows with
+// query_blocks blocks of 16 each.
+inline int f32_groups(int query_rows, int query_blocks) { return ((query_rows + 15) / 16 + query_blocks - 1) / query_blocks; }
 
 // State of one stream kept on the device for device-planned steps (the host's
 // per-stream mirror, moved to the device while the caller drives the cache
@@ -217,7 +220,11 @@ hipError_t launch_attn_tile(const DevState& st, const AttnBatch& b, const void* 
 // 128; the step's rows already stored); split partials as launch_attn_tile's.
 hipError_t launch_attn_block(const DevState& st, const AttnBatch& b, const void* q, void* o,
                              hipStream_t stream, const KTimer& kt);
-// VALU attention, one (row, kv head) per workgroup column (fp32 caches, decode).
+// MFMA attention of fp32 caches (chunk and decode, D 64 or 128), query_blocks (1 or
+// 2) blocks of 16 query rows per workgroup; with k_in/v_in non-null it also appends, like launch_attn_tile.  Split partials as launch_attn_valu's.
+hipError_t launch_attn_f32(const DevState& st, const AttnBatch& b, int query_blocks, const void* q, void* o,
+                           const void* k_in, const void* v_in, hipStream_t stream, const KTimer& kt);
+// VALU attention of bf16 caches, one (row, kv head) per workgroup column.
 hipError_t launch_attn_valu(const DevState& st, const AttnBatch& b, const void* q, void* o,
                             hipStream_t stream, const KTimer& kt);
 // h16: the partials come from the MFMA kernel (fp16 O rows), else from the VALU kernel (fp32)

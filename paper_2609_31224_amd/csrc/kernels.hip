@@ -12,7 +12,7 @@
 //               shuffles, key splits for parallelism; also bf16 decode (one
 //               query row per stream).
 //   attn_valu   the same attention on the vector ALU, one query row per
-//               workgroup column: fp32 caches (chunk and decode).
+//               workgroup column (bf16 caches under A2T_FORCE_VALU).
 //   attn_merge  combines key-split partials (fixed order, deterministic): split
 //               groups combined in LDS, or one thread per row walking every
 //               split when a launch's streams have few splits.
@@ -1559,15 +1559,9 @@ static hipError_t valu_dispatch_g(const DevState& st, const B& b, const void* q,
 hipError_t launch_attn_valu(const DevState& st, const AttnBatch& b, const void* q, void* o,
                             hipStream_t stream, const KTimer& kt) {
     return by_size<AttnBatchT>(b, [&](const auto& bb) {
-        using B = std::decay_t<decltype(bb)>;
-        if (st.dtype == 0) {
-            if (st.D == 128) return valu_dispatch_g<float, 128>(st, bb, q, o, stream, kt);
-            if (st.D == 64) return valu_dispatch_g<float, 64>(st, bb, q, o, stream, kt);
-        } else {
-            if (st.D == 128) return valu_dispatch_g<bf16_t, 128>(st, bb, q, o, stream, kt);
-            if (st.D == 64) return valu_dispatch_g<bf16_t, 64>(st, bb, q, o, stream, kt);
-        }
-        (void)sizeof(B);
+        if (st.dtype != 1) return hipErrorInvalidValue;
+        if (st.D == 128) return valu_dispatch_g<bf16_t, 128>(st, bb, q, o, stream, kt);
+        if (st.D == 64) return valu_dispatch_g<bf16_t, 64>(st, bb, q, o, stream, kt);
         return hipErrorInvalidValue;
     });
 }
