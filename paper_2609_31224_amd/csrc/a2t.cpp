@@ -672,7 +672,7 @@ void free_device(a2t_cache* c) {
         if (c->dev.v_unit) (void)hipFree(c->dev.v_unit);
     }
     void* ptrs[] = {c->dev.unit_pos, c->dev.unit_uid, c->dev.unit_seg, c->dev.kept_pos,
-                    c->dev.kept_uid, c->dev.kept_seg, c->dev.rope, c->dev.ev_mask,
+                    c->dev.kept_uid, c->dev.kept_seg, c->dev.rope, c->dev.inv_freq, c->dev.ev_mask,
                     c->dev.ev_slot, c->dev.ws, c->dev.dss, c->dplan};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -820,6 +820,7 @@ int a2t_cache_create(const a2t_config* cfg, void* hip_stream, a2t_cache** out) {
     alloc((void**)&d.kept_pos, S * std::max(1, k.kept_rows) * 4);
     alloc((void**)&d.kept_uid, S * std::max(1, k.kept_rows) * 4);
     alloc((void**)&d.kept_seg, S * std::max(1, k.kept_rows));
+    alloc((void**)&d.inv_freq, (k.head_dim / 2) * 8);
     alloc((void**)&d.rope, S * k.max_step_rows * (k.head_dim / 2) * 8);
     alloc((void**)&d.ev_mask, S * tot);
     alloc((void**)&d.ev_slot, S * tot * 4);
@@ -851,6 +852,12 @@ int a2t_cache_create(const a2t_config* cfg, void* hip_stream, a2t_cache** out) {
         delete c;
         (void)hipGetLastError();
         return A2T_ERR_OOM;
+    }
+    // waited for: later steps may run on another stream
+    if (launch_inv_freq(d, c->stream) != hipSuccess || hipStreamSynchronize(c->stream) != hipSuccess) {
+        free_device(c);
+        delete c;
+        return A2T_ERR_HIP;
     }
     *out = c;
     return A2T_OK;

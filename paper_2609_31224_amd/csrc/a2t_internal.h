@@ -63,6 +63,7 @@ struct DevState {
     int32_t unit_rows, kept_rows, max_step_rows;
     float scale_log2e;  // softmax scale * log2(e)
     double theta;
+    double* inv_freq;   // [D / 2] theta^(-2i/D)
 };
 
 __host__ __device__ inline int64_t pool_index(const DevState& st, int layer, int s, int g,
@@ -204,6 +205,8 @@ struct KTimer {
     hipEvent_t stop = nullptr;
 };
 
+// Fills st.inv_freq (once per cache).
+hipError_t launch_inv_freq(const DevState& st, hipStream_t stream);
 // Launchers (kernels.hip).  Each issues one kernel and returns the hipError_t
 // of the launch.
 hipError_t launch_step_meta(const DevState& st, const StepBatch& b, const uint8_t* seg,
