@@ -400,10 +400,9 @@ constexpr int kBlockTilesPerCu = 6;
 bool many_rows(const a2t_cache* c, int n, const int32_t* ids, const int32_t* n_q) {
     if (c->cfg.dtype != A2T_BF16 || c->force_valu) return false;
     const int G = c->cfg.n_q_heads / c->cfg.n_kv_heads;
-    int rows = 0;
-    int64_t tiles = 0;
+    int64_t rows = 0, tiles = 0;   // row counts are not checked yet where an append follows
     for (int i = 0; i < n; ++i) {
-        rows = std::max(rows, n_q[i]);
+        rows = std::max<int64_t>(rows, n_q[i]);
         tiles += (c->ss[ids[i]].resident() + kTileKeys - 1) / kTileKeys;
     }
     return G * rows > 2 * kBlockRows ||
@@ -1059,6 +1058,7 @@ int a2t_chunk_attn(a2t_cache* c, int32_t layer, int32_t n_streams, const int32_t
 
 namespace {
 
+// The caller has checked the arguments (append_attn_args) and the stream ids.
 int append_attn_impl(a2t_cache* c, int32_t layer, int32_t n_streams, const int32_t* ids,
                      const int32_t* n_rows, const void* kin, const void* vin, const uint8_t* seg,
                      const int32_t* pos, const int32_t* unit_id, const int32_t* n_q, const void* q,
@@ -1114,7 +1114,7 @@ int a2t_append_attn(a2t_cache* c, int32_t layer, int32_t n_streams, const int32_
                     const int32_t* pos, const int32_t* unit_id, const int32_t* n_q,
                     const void* q, void* o) {
     int rc = append_attn_args(c, layer, n_streams, n_rows, n_q, q, o);
-    if (rc) return rc;
+    if (rc || (rc = check_streams(c, n_streams, ids))) return rc;
     return append_attn_impl(c, layer, n_streams, ids, n_rows, kin, vin, seg, pos, unit_id, n_q, q,
                             o, nullptr);
 }
