@@ -146,8 +146,13 @@ __device__ __forceinline__ void store_chunk(bf16_t* row, int c, const float (&g)
 }
 
 // Running sums in the log2 domain: z = sum 2^(k x - m) with m at least the largest
-// k x so far (-inf: nothing yet).  m is the reference exactly as it was subtracted,
-// so log2 of the whole sum is m + log2 z with no error from rounding k x.
+// k x so far, rounded.  m is the reference exactly as it was subtracted, so log2 of the
+// whole sum is m + log2 z with no error from rounding k x.  The rounding moves the
+// exponents by up to ulp(m) / 2, which is nothing at kFar (2^-5) and would overflow at
+// 2^32: m starts at -kFar, below which a logit counts as 0 beside any other (masks of
+// -1e30 or of the type's lowest value), and a row whose m ends up at kFar or further
+// out is computed again from exact differences (the kernel's end).
+constexpr float kFar = 1048576.f;
 struct Sum {
     float m, z;
 };
@@ -155,7 +160,6 @@ struct Sum {
 struct SumA {
     float m, z, a;
 };
-__device__ __forceinline__ float finite_ref(float m) { return m == -INFINITY ? 0.f : m; }
 __device__ __forceinline__ float exp2_(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // largest logit of a chunk, and of mx
@@ -170,11 +174,11 @@ __device__ __forceinline__ float max_of(const Raw<T>& r, const Apart& ap, float 
 // raises the reference to the largest logit mx of the chunks about to be added
 __device__ __forceinline__ void raise(Sum& s, float mx, float k) {
     const float mn = fmaxf(s.m, mx * k);
-    s.z *= exp2_(s.m - finite_ref(mn));
+    s.z *= exp2_(s.m - mn);
     s.m = mn;
 }
 __device__ __forceinline__ void raise(SumA& w, float mx, float k) {
-    const float mn = fmaxf(w.m, mx * k), sc = exp2_(w.m - finite_ref(mn));
+    const float mn = fmaxf(w.m, mx * k), sc = exp2_(w.m - mn);
     w.z *= sc;
     w.a *= sc;
     w.m = mn;
@@ -182,23 +186,21 @@ __device__ __forceinline__ void raise(SumA& w, float mx, float k) {
 // adds a chunk of the student
 template <typename T>
 __device__ __forceinline__ void add(Sum& s, const Raw<T>& r, const Apart& ap, float k) {
-    const float ref = finite_ref(s.m);
     float x[kChunk], z = 0.f;
     unpack(r, ap, x);
 #pragma unroll
-    for (int e = 0; e < kChunk; ++e) z += exp2_(fmaf(x[e], k, -ref));
+    for (int e = 0; e < kChunk; ++e) z += exp2_(fmaf(x[e], k, -s.m));
     s.z += z;
 }
 // adds a chunk of the teacher t beside the student s
 template <typename T>
 __device__ __forceinline__ void add(SumA& w, const Raw<T>& t, const Raw<T>& s, const Apart& ap, float k) {
-    const float ref = finite_ref(w.m);
     float x[kChunk], y[kChunk], z = 0.f, a = 0.f;
     unpack(t, ap, x);
     unpack(s, ap, y);
 #pragma unroll
     for (int e = 0; e < kChunk; ++e) {
-        const float p = exp2_(fmaf(x[e], k, -ref));
+        const float p = exp2_(fmaf(x[e], k, -w.m));
         z += p;
         // a token the teacher rules out (and the added ones) contributes nothing
         a += x[e] == -INFINITY ? 0.f : p * (x[e] - y[e]);
@@ -207,13 +209,13 @@ __device__ __forceinline__ void add(SumA& w, const Raw<T>& t, const Raw<T>& s, c
     w.a += a;
 }
 __device__ __forceinline__ void merge(Sum& x, const Sum& y) {
-    const float mn = fmaxf(x.m, y.m), ref = finite_ref(mn);
-    x.z = x.z * exp2_(x.m - ref) + y.z * exp2_(y.m - ref);
+    const float mn = fmaxf(x.m, y.m);
+    x.z = x.z * exp2_(x.m - mn) + y.z * exp2_(y.m - mn);
     x.m = mn;
 }
 __device__ __forceinline__ void merge(SumA& x, const SumA& y) {
-    const float mn = fmaxf(x.m, y.m), ref = finite_ref(mn);
-    const float cx = exp2_(x.m - ref), cy = exp2_(y.m - ref);
+    const float mn = fmaxf(x.m, y.m);
+    const float cx = exp2_(x.m - mn), cy = exp2_(y.m - mn);
     x.z = x.z * cx + y.z * cy;
     x.a = x.a * cx + y.a * cy;
     x.m = mn;
@@ -302,10 +304,12 @@ __global__ __launch_bounds__(kRowThreads) void distill_row_kernel(
     for (int k = 0; k < NR; ++k) cut_student(hs[k], chunk_no(k), k * TH);
 
     const Apart to_max, to_sum;
-    Sum u{-INFINITY, 0.f};
-    if (wk == 0.f) {
+    const bool native = wk != 0.f;
+    const float kt = inv_t * kLog2e, tt = 1.f / inv_t;
+    if (!native) {
         // ---- transcription row: the student at temperature 1
         constexpr float k1 = kLog2e;
+        Sum u{-kFar, 0.f};
 #pragma unroll
         for (int k = 0; k < NR; k += 4) {   // in groups of four chunks
             constexpr int N = 4;
@@ -330,116 +334,179 @@ __global__ __launch_bounds__(kRowThreads) void distill_row_kernel(
             add(u, x, to_sum, k1);
         }
         reduce(u, nullptr, part);
-        if (tid == 0) rowval[blockIdx.x] = make_float2(kLn2 * (u.m + __builtin_amdgcn_logf(u.z)) - target_logit, 0.f);
-        if (!GRAD) return;
-        // dL/ds_v = wc (softmax(s)_v - [v == target])
-        const float coef = wc / u.z, ref = finite_ref(u.m);
-        const Apart to_write;
-        auto write = [&](const Raw<T>& x, int c) {
-            float y[kChunk];
-            unpack(x, to_write, y);
+        if (fabsf(u.m) < kFar) {
+            if (tid == 0) rowval[blockIdx.x] = make_float2(kLn2 * (u.m + __builtin_amdgcn_logf(u.z)) - target_logit, 0.f);
+            if (!GRAD) return;
+            // dL/ds_v = wc (softmax(s)_v - [v == target])
+            const float coef = wc / u.z;
+            const Apart to_write;
+            auto write = [&](const Raw<T>& x, int c) {
+                float y[kChunk];
+                unpack(x, to_write, y);
 #pragma unroll
-            for (int e = 0; e < kChunk; ++e) y[e] = coef * exp2_(fmaf(y[e], k1, -ref));
-            if (c == r.target / kChunk) {
+                for (int e = 0; e < kChunk; ++e) y[e] = coef * exp2_(fmaf(y[e], k1, -u.m));
+                if (c == r.target / kChunk) {
 #pragma unroll
-                for (int e = 0; e < kChunk; ++e) y[e] -= e == r.target % kChunk ? wc : 0.f;
+                    for (int e = 0; e < kChunk; ++e) y[e] -= e == r.target % kChunk ? wc : 0.f;
+                }
+                if (c < nc) store_chunk(g, c, y);
+            };
+#pragma unroll
+            for (int k = 0; k < NR; ++k)
+            {
+                if (k * TH < nc) write(hs[k], chunk_no(k));
+                in_turn();
             }
-            if (c < nc) store_chunk(g, c, y);
-        };
+            for (int c = NR * TH + tid; c - tid < nc; c += TH) {
+                Raw<T> x = student_chunk(c);
+                cut_student(x, c, c - tid);
+                write(x, c);
+            }
+            return;
+        }
+    } else {
+        // ---- native row: student and teacher at temperature T
+        Sum u{-kFar, 0.f};
+        SumA w{-kFar, 0.f, 0.f};
+        constexpr int NA = Hold<T>::kAhead;
+        Raw<T> ts[NR];   // in flight: NA chunks ahead of the one in work
 #pragma unroll
-        for (int k = 0; k < NR; ++k)
-        {
-            if (k * TH < nc) write(hs[k], chunk_no(k));
+        for (int k = 0; k < NA; ++k) ts[k] = teacher_chunk(chunk_no(k));
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            if (k + NA < NR) ts[k + NA] = teacher_chunk(chunk_no(k + NA));
+            const int c = chunk_no(k);
+            Raw<T> x = ts[k];
+            cut_teacher(x, c, k * TH);
+            if (GRAD && k < NL) reinterpret_cast<Raw<T>*>(t_lds)[c] = x;
+            float mu = -INFINITY, mw = -INFINITY;
+            if (k * TH < nc) {
+                mu = max_of(hs[k], to_max, mu);
+                mw = max_of(x, to_max, mw);
+            }
+            if (k * TH < nc) {
+                raise(u, mu, kt);
+                add(u, hs[k], to_sum, kt);
+                raise(w, mw, kt);
+                add(w, x, hs[k], to_sum, kt);
+            }
             in_turn();
         }
         for (int c = NR * TH + tid; c - tid < nc; c += TH) {
-            Raw<T> x = student_chunk(c);
+            Raw<T> x = student_chunk(c), y = teacher_chunk(c);
             cut_student(x, c, c - tid);
-            write(x, c);
+            cut_teacher(y, c, c - tid);
+            raise(u, max_of(x, to_max, -INFINITY), kt);
+            add(u, x, to_sum, kt);
+            raise(w, max_of(y, to_max, -INFINITY), kt);
+            add(w, y, x, to_sum, kt);
         }
-        return;
+        reduce(u, &w, part);
+        if (fabsf(u.m) < kFar && fabsf(w.m) < kFar) {
+            if (tid == 0) {
+                const float lse = (u.m - w.m) + (__builtin_amdgcn_logf(u.z) - __builtin_amdgcn_logf(w.z));
+                rowval[blockIdx.x] = make_float2(0.f, tt * tt * (inv_t * w.a / w.z + kLn2 * lse));
+            }
+            if (!GRAD) return;
+            // dL/ds_v = wk T (softmax(u)_v - p_t,v)
+            const float cu = wk * tt / u.z, cw = wk * tt / w.z;
+            const Apart to_write;
+            auto write = [&](const Raw<T>& x, const Raw<T>& y, int c) {
+                float a[kChunk], b[kChunk];
+                unpack(x, to_write, a);
+                unpack(y, to_write, b);
+#pragma unroll
+                for (int e = 0; e < kChunk; ++e)
+                    a[e] = cu * exp2_(fmaf(a[e], kt, -u.m)) - cw * exp2_(fmaf(b[e], kt, -w.m));
+                if (c < nc) store_chunk(g, c, a);
+            };
+#pragma unroll
+            for (int k = NL; k < NL + NA; ++k) ts[k] = teacher_chunk(chunk_no(k));
+#pragma unroll
+            for (int k = 0; k < NR; ++k) {
+                // the chunks that LDS holds are written while the others are on their way
+                if (k >= NL && k + NA < NR) ts[k + NA] = teacher_chunk(chunk_no(k + NA));
+                if (k * TH < nc) {
+                    const int c = chunk_no(k);
+                    Raw<T> y;
+                    if (k < NL) {
+                        y = reinterpret_cast<const Raw<T>*>(t_lds)[c];   // written by this thread
+                    } else {
+                        y = ts[k];
+                        cut_teacher(y, c, k * TH);
+                    }
+                    write(hs[k], y, c);
+                }
+                in_turn();
+            }
+            for (int c = NR * TH + tid; c - tid < nc; c += TH) {
+                Raw<T> x = student_chunk(c), y = teacher_chunk(c);
+                cut_student(x, c, c - tid);
+                cut_teacher(y, c, c - tid);
+                write(x, y, c);
+            }
+            return;
+        }
     }
 
-    // ---- native row: student and teacher at temperature T
-    const float kt = inv_t * kLog2e;
-    SumA w{-INFINITY, 0.f, 0.f};
-    constexpr int NA = Hold<T>::kAhead;
-    Raw<T> ts[NR];   // in flight: NA chunks ahead of the one in work
-#pragma unroll
-    for (int k = 0; k < NA; ++k) ts[k] = teacher_chunk(chunk_no(k));
-#pragma unroll
-    for (int k = 0; k < NR; ++k) {
-        if (k + NA < NR) ts[k + NA] = teacher_chunk(chunk_no(k + NA));
-        const int c = chunk_no(k);
-        Raw<T> x = ts[k];
-        cut_teacher(x, c, k * TH);
-        if (GRAD && k < NL) reinterpret_cast<Raw<T>*>(t_lds)[c] = x;
-        float mu = -INFINITY, mw = -INFINITY;
-        if (k * TH < nc) {
-            mu = max_of(hs[k], to_max, mu);
-            mw = max_of(x, to_max, mw);
+    // ---- a row with a largest k x of kFar or beyond, or none above -kFar: the largest logits
+    // first, then sums of 2^(k (x - largest)), whose differences are exact or far below 0
+    const T* const other = native ? t : s;   // a transcription row has no use for its second row
+    const int others = native ? vocab : vs;
+    auto each = [&](auto f) {
+        for (int c = tid; c < nc; c += TH) {
+            Raw<T> x = load_raw(s, c), y = load_raw(other, min(c, (others - 1) / kChunk));
+            cut(x, vs - c * kChunk);
+            cut(y, others - c * kChunk);
+            float a[kChunk], b[kChunk];
+            unpack(x, to_sum, a);
+            unpack(y, to_sum, b);
+            f(c, a, b);
         }
-        if (k * TH < nc) {
-            raise(u, mu, kt);
-            add(u, hs[k], to_sum, kt);
-            raise(w, mw, kt);
-            add(w, x, hs[k], to_sum, kt);
-        }
-        in_turn();
-    }
-    for (int c = NR * TH + tid; c - tid < nc; c += TH) {
-        Raw<T> x = student_chunk(c), y = teacher_chunk(c);
-        cut_student(x, c, c - tid);
-        cut_teacher(y, c, c - tid);
-        raise(u, max_of(x, to_max, -INFINITY), kt);
-        add(u, x, to_sum, kt);
-        raise(w, max_of(y, to_max, -INFINITY), kt);
-        add(w, y, x, to_sum, kt);
-    }
-    reduce(u, &w, part);
-    const float tt = 1.f / inv_t;
-    if (tid == 0) {
-        const float lse = (u.m - w.m) + (__builtin_amdgcn_logf(u.z) - __builtin_amdgcn_logf(w.z));
-        rowval[blockIdx.x] = make_float2(0.f, tt * tt * (inv_t * w.a / w.z + kLn2 * lse));
-    }
-    if (!GRAD) return;
-    // dL/ds_v = wk T (softmax(u)_v - p_t,v)
-    const float cu = wk * tt / u.z, cw = wk * tt / w.z, ru = finite_ref(u.m), rw = finite_ref(w.m);
-    const Apart to_write;
-    auto write = [&](const Raw<T>& x, const Raw<T>& y, int c) {
-        float a[kChunk], b[kChunk];
-        unpack(x, to_write, a);
-        unpack(y, to_write, b);
-#pragma unroll
-        for (int e = 0; e < kChunk; ++e)
-            a[e] = cu * exp2_(fmaf(a[e], kt, -ru)) - cw * exp2_(fmaf(b[e], kt, -rw));
-        if (c < nc) store_chunk(g, c, a);
     };
+    const float kx = native ? kt : kLog2e;
+    float ms = -INFINITY, mt = -INFINITY, zs = 0.f, zt = 0.f, at = 0.f;
+    each([&](int, const float(&a)[kChunk], const float(&b)[kChunk]) {
 #pragma unroll
-    for (int k = NL; k < NL + NA; ++k) ts[k] = teacher_chunk(chunk_no(k));
+        for (int e = 0; e < kChunk; ++e) ms = fmaxf(ms, a[e]), mt = fmaxf(mt, b[e]);
+    });
+    const auto over_row = [&](float us, float uz, float wm, float wz, float wa, float (&out)[5]) {
+        Sum u{us, uz};
+        SumA w{wm, wz, wa};
+        __syncthreads();
+        reduce(u, &w, part);
+        out[0] = u.m, out[1] = u.z, out[2] = w.m, out[3] = w.z, out[4] = w.a;
+    };
+    float all[5];
+    over_row(ms, 0.f, mt, 0.f, 0.f, all);
+    ms = all[0], mt = all[2];
+    each([&](int, const float(&a)[kChunk], const float(&b)[kChunk]) {
 #pragma unroll
-    for (int k = 0; k < NR; ++k) {
-        // the chunks that LDS holds are written while the others are on their way
-        if (k >= NL && k + NA < NR) ts[k + NA] = teacher_chunk(chunk_no(k + NA));
-        if (k * TH < nc) {
-            const int c = chunk_no(k);
-            Raw<T> y;
-            if (k < NL) {
-                y = reinterpret_cast<const Raw<T>*>(t_lds)[c];   // written by this thread
-            } else {
-                y = ts[k];
-                cut_teacher(y, c, k * TH);
-            }
-            write(hs[k], y, c);
+        for (int e = 0; e < kChunk; ++e) {
+            zs += exp2_((a[e] - ms) * kx);
+            const float p = exp2_((b[e] - mt) * kx);
+            zt += p;
+            at += b[e] == -INFINITY ? 0.f : p * ((b[e] - a[e]) * inv_t);
         }
-        in_turn();
-    }
-    for (int c = NR * TH + tid; c - tid < nc; c += TH) {
-        Raw<T> x = student_chunk(c), y = teacher_chunk(c);
-        cut_student(x, c, c - tid);
-        cut_teacher(y, c, c - tid);
-        write(x, y, c);
-    }
+    });
+    over_row(0.f, zs, 0.f, zt, at, all);
+    zs = all[1], zt = all[3], at = all[4];
+    const float lu = kLn2 * __builtin_amdgcn_logf(zs), lw = kLn2 * __builtin_amdgcn_logf(zt);
+    if (tid == 0)
+        rowval[blockIdx.x] = native ? make_float2(0.f, tt * tt * (at / zt + (ms - mt) * inv_t + (lu - lw)))
+                                    : make_float2((ms - target_logit) + lu, 0.f);
+    if (!GRAD) return;
+    const float cu = (native ? wk * tt : wc) / zs, cw = native ? wk * tt / zt : 0.f;
+    each([&](int c, const float(&a)[kChunk], const float(&b)[kChunk]) {
+        float y[kChunk];
+#pragma unroll
+        for (int e = 0; e < kChunk; ++e) {
+            y[e] = cu * exp2_((a[e] - ms) * kx);
+            if (native) y[e] -= cw * exp2_((b[e] - mt) * kx);
+            else if (c * kChunk + e == r.target) y[e] -= wc;
+        }
+        store_chunk(g, c, y);
+    });
 }
 
 // one workgroup: sum_i c_asr ce_i, c_nat kl_i, c_dec kl_i, c_turn kl_i in a fixed order

@@ -64,3 +64,52 @@ def test_ruled_out_tokens(gpu, dtype):
     lo, gr, _ = _run(b, vocab, 2, dtype, 1.0)
     _check_losses(lo, ref.losses)
     _check_grad(gr[:, :vocab + 2], ref.grad, dtype)
+
+
+def _rounded(x, dtype):
+    import torch
+    t = torch.from_numpy(np.asarray(x, np.float32))
+    return (t if dtype == "f32" else t.bfloat16().float()).numpy()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T", [0.5, 1.0, 2.0])
+@pytest.mark.parametrize("mask", [-1e10, -1e30, "lowest"])
+def test_masked_spans(gpu, dtype, T, mask):
+    """Logits masked by a large finite value instead of -inf, in spans that leave some
+    threads of a row's workgroup nothing else."""
+    import torch
+    if mask == "lowest":
+        mask = torch.finfo(torch.float32 if dtype == "f32" else torch.bfloat16).min
+    vocab, added = 1500, 2
+    b = make_distill_batch(seed=24, n_utt=2, units=3, vocab=vocab, added=added, dtype=dtype)
+    student, teacher = b.student.copy(), b.teacher.copy()
+    for x in (student, teacher):
+        x[:, 40:1400] = _rounded(mask, dtype)
+    b = type(b)(student, teacher, b.kind, np.where((b.target >= 40) & (b.target < 1400), 7, b.target).astype(np.int32),
+                b.dec_group, b.turn_group)
+    _check(b, vocab, added, dtype, T)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T,offset", [(1.0, 3e9), (0.5, -3e9), (2.0, 1e12), (1.0, -1e30), (1e-6, 0.0)])
+def test_far_logits(gpu, dtype, T, offset):
+    """Rows whose logits all lie far from 0, or far apart at the temperature (also with rows
+    past the register capacity): exponents come from differences, not from the logits."""
+    for vocab in (1500, 64 * 19 * 8 + 77):
+        b = make_distill_batch(seed=25, n_utt=1, units=3, vocab=vocab, added=2, dtype=dtype)
+        b = type(b)(_rounded(b.student * 3 + offset, dtype), _rounded(b.teacher * 3 + offset, dtype), b.kind, b.target,
+                    b.dec_group, b.turn_group)
+        _check(b, vocab, 2, dtype, T)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_rows_of_the_lowest_value(gpu, dtype):
+    """Transcription rows without a single unmasked logit are uniform."""
+    import torch
+    low = torch.finfo(torch.float32 if dtype == "f32" else torch.bfloat16).min
+    vocab, added = 700, 2
+    b = make_distill_batch(seed=26, n_utt=1, units=3, vocab=vocab, added=added, dtype=dtype)
+    student = b.student.copy()
+    student[b.target >= 0] = low
+    _check(type(b)(student, b.teacher, b.kind, b.target, b.dec_group, b.turn_group), vocab, added, dtype, 1.0)
