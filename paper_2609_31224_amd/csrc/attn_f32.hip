@@ -48,6 +48,13 @@ __device__ __forceinline__ f32x4 gload(const float* p) {
     return *reinterpret_cast<const __attribute__((address_space(1))) f32x4*>(reinterpret_cast<uintptr_t>(p));
 }
 
+// LDS accesses of the wave before this one come before those after it, whatever the compiler
+// knows about their addresses in one lane (the hardware keeps a wave's LDS accesses in order)
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // max / sum over the four lanes l % 16 + 16 i that hold one query column
 __device__ __forceinline__ float col_max(float x) {
     const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -234,6 +241,7 @@ __global__ __launch_bounds__(64 * kKeyWaves, 2) void attn_f32_kernel(DevState st
             const int l16 = ln & 15, lg = ln >> 4;
 #pragma unroll
             for (int i2 = 0; i2 < KS; ++i2) k_at((64 * i2 + ln) / CPR, ln % CPR) = kc[i2];
+            wave_lds_order();   // other lanes read these rows
             if (i + 1 < n) load_k(kb + kStride, ln);
             if (d.n_new > 0 && kb + kKeyBlock > newbase) {
                 // rotate the keys that are new (the rotate-half partner of a lane's chunk s
