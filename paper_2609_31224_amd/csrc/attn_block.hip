@@ -96,7 +96,7 @@ __global__ __launch_bounds__(kBlockThreads) void attn_block_kernel(DevState st, 
     constexpr int RPB = 512 / D;               // rows per 1 KiB DMA block
     constexpr int OPS = kTileKeys / RPB / 4;   // K (and V) DMA blocks per wave and tile
     constexpr int TILE = kTileKeys * D;
-        __shared__ __align__(1024) uint16_t ring[8 * TILE];   // per key half two K and two V stages
+    __shared__ __align__(1024) uint16_t ring[8 * TILE];   // per key half two K and two V stages
     __shared__ float2 s_ml[4][64];
     static_assert(8 * TILE * 2 >= 4 * DB * 16 * 256, "the second key half's sums fit the ring");
 
@@ -174,16 +174,16 @@ __global__ __launch_bounds__(kBlockThreads) void attn_block_kernel(DevState st, 
     };
     static_assert((RPB == 4 && OPS == 4) || (RPB == 8 && OPS == 2), "the offsets of a wave's DMA blocks");
     // a key half's waves load and read their own tiles only: tile i of half kh is
-    // t0 + 2 i + kh (past the range: the last tile again, fully masked)
+    // t0 + 2 i + kh (the second half of an odd count has one less)
     const int n = (t1 - t0 + 1) / 2;
     uint16_t* const ring_k = ring + kh * 4 * TILE;   // two K stages, two V stages
     uint16_t* const ring_v = ring_k + 2 * TILE;
     // K and V of tile i, if it is in the range
     auto issue_kv = [&](int i) {
-        if (i < n) {
+        const int t = t0 + 2 * i + kh;
+        if (t < t1) {
 #pragma unroll 1
-            for (int x = 0; x < 2; ++x)
-                issue(min(t0 + 2 * i + kh, t1 - 1), x, ring_k + (2 * x + (i & 1)) * TILE);
+            for (int x = 0; x < 2; ++x) issue(t, x, ring_k + (2 * x + (i & 1)) * TILE);
         }
     };
     issue_kv(0);
@@ -287,14 +287,13 @@ __global__ __launch_bounds__(kBlockThreads) void attn_block_kernel(DevState st, 
         }
     };
     auto softmax = [&](int t) {
-        const bool skip = t >= t1;
-        if (skip || t * kTileKeys + kTileKeys - 1 > lim_w) {
-            const int k0 = t * kTileKeys + 4 * h, last = skip ? -1 : lim;
+        if (t * kTileKeys + kTileKeys - 1 > lim_w) {
+            const int k0 = t * kTileKeys + 4 * h;
 #pragma unroll
             for (int blk = 0; blk < 2; ++blk)
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
-                    if (k0 + 32 * blk + 8 * (r >> 2) + (r & 3) > last) sc[blk][r] = -INFINITY;
+                    if (k0 + 32 * blk + 8 * (r >> 2) + (r & 3) > lim) sc[blk][r] = -INFINITY;
         }
         float m4[4];
 #pragma unroll
@@ -334,6 +333,7 @@ __global__ __launch_bounds__(kBlockThreads) void attn_block_kernel(DevState st, 
     for (int i = 0; i < n; ++i) {
         wait_vmem<0>();
         barrier_only();
+        if (t0 + 2 * i + kh >= t1) break;   // the last round of an odd count
         k_issue(ring_k + stage * TILE, I0{}, ka);
         k_issue(ring_k + stage * TILE, I1{}, kc);
         issue_kv(i + 1);

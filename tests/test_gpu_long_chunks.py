@@ -104,3 +104,33 @@ def test_long_chunks_without_workspace(gpu):
         a2t.a2t_cache_destroy(c)
     assert np.abs(outs[0] - outs[1]).max() <= BF16_TOL
     assert np.abs(outs[0] - outs[2]).max() <= BF16_TOL
+
+
+@pytest.mark.parametrize("d,splits", [(64, "1"), (128, "1"), (128, "3"), (64, None)])
+def test_infinite_values(gpu, d, splits, monkeypatch):
+    """Row `bad` holds an infinite value in its first dim, in the last of an odd number of key
+    tiles: the rows that see it get an infinity there and are otherwise as if it were finite;
+    the blocks that end before its tile are untouched."""
+    import numpy as np
+    import torch
+    import paper_2609_31224_amd as a2t
+    if splits:
+        monkeypatch.setenv("A2T_SPLITS", splits)
+    rows, hq, hkv, bad = 290, 4, 1, 270      # 5 tiles of keys, 10 blocks of 32 rows
+    g = torch.Generator(device="cuda").manual_seed(3)
+    k, v, q = (torch.randn((rows, h, d), generator=g, device="cuda").bfloat16() for h in (hkv, hkv, hq))
+    seg, pos = np.full(rows, SEG_ACOUSTIC, np.uint8), np.arange(rows)
+    outs = []
+    for spoil in (False, True):
+        vv = v.clone()
+        if spoil:
+            vv[bad, :, 0] = float("inf")
+        c = a2t.a2t_cache_create(1, 1, hq, hkv, d, a2t.A2T_BF16, 2 * rows, 8, rows)
+        o = torch.zeros_like(q)
+        a2t.a2t_append_attn(c, 0, [0], [rows], k, vv, seg, pos, [0], [rows], q, o)
+        a2t.a2t_sync(c)
+        outs.append(o.float().cpu().numpy())
+        a2t.a2t_cache_destroy(c)
+    assert np.isposinf(outs[1][bad:, :, 0]).all()
+    assert np.array_equal(outs[0][:, :, 1:], outs[1][:, :, 1:])
+    assert np.array_equal(outs[0][:256, :, 0], outs[1][:256, :, 0])   # whole blocks of 128 query rows
