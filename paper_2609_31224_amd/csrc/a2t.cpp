@@ -113,6 +113,7 @@ struct a2t_cache {
     hipStream_t stream = nullptr;
     int poisoned = 0;
     DevState dev{};
+    RopeFreq freq{};
     std::vector<StreamState> ss;
     // pinned staging slots for step metadata, reused round-robin behind events
     uint8_t* stage = nullptr;      // host address
@@ -671,7 +672,7 @@ void free_device(a2t_cache* c) {
         if (c->dev.v_unit) (void)hipFree(c->dev.v_unit);
     }
     void* ptrs[] = {c->dev.unit_pos, c->dev.unit_uid, c->dev.unit_seg, c->dev.kept_pos,
-                    c->dev.kept_uid, c->dev.kept_seg, c->dev.rope, c->dev.inv_freq, c->dev.ev_mask,
+                    c->dev.kept_uid, c->dev.kept_seg, c->dev.rope, c->dev.ev_mask,
                     c->dev.ev_slot, c->dev.ws, c->dev.dss, c->dplan};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -768,7 +769,7 @@ int a2t_cache_create(const a2t_config* cfg, void* hip_stream, a2t_cache** out) {
     d.unit_rows = k.unit_rows;
     d.kept_rows = k.kept_rows;
     d.max_step_rows = k.max_step_rows;
-    d.theta = c->cfg.rope_theta;
+    for (int i = 0; i < k.head_dim / 2; ++i) c->freq.f[i] = std::pow(c->cfg.rope_theta, (-2.0 * i) / k.head_dim);
     d.scale_log2e = (float)(c->cfg.attn_scale * 1.4426950408889634);
     if (c->host_only) {
         *out = c;
@@ -819,7 +820,6 @@ int a2t_cache_create(const a2t_config* cfg, void* hip_stream, a2t_cache** out) {
     alloc((void**)&d.kept_pos, S * std::max(1, k.kept_rows) * 4);
     alloc((void**)&d.kept_uid, S * std::max(1, k.kept_rows) * 4);
     alloc((void**)&d.kept_seg, S * std::max(1, k.kept_rows));
-    alloc((void**)&d.inv_freq, (k.head_dim / 2) * 8);
     alloc((void**)&d.rope, S * k.max_step_rows * (k.head_dim / 2) * 8);
     alloc((void**)&d.ev_mask, S * tot);
     alloc((void**)&d.ev_slot, S * tot * 4);
@@ -851,12 +851,6 @@ int a2t_cache_create(const a2t_config* cfg, void* hip_stream, a2t_cache** out) {
         delete c;
         (void)hipGetLastError();
         return A2T_ERR_OOM;
-    }
-    // waited for: later steps may run on another stream
-    if (launch_inv_freq(d, c->stream) != hipSuccess || hipStreamSynchronize(c->stream) != hipSuccess) {
-        free_device(c);
-        delete c;
-        return A2T_ERR_HIP;
     }
     *out = c;
     return A2T_OK;
@@ -1005,7 +999,7 @@ static int append_impl(a2t_cache* c, int32_t layer, int32_t n_streams, const int
             hipError_t e;
             {
                 ProfScope ps(c, "step_meta");
-                e = launch_step_meta(c->dev, sb, reinterpret_cast<const uint8_t*>(sseg) + shift,
+                e = launch_step_meta(c->dev, c->freq, sb, reinterpret_cast<const uint8_t*>(sseg) + shift,
                                      reinterpret_cast<const int32_t*>(reinterpret_cast<uint8_t*>(spos) + shift),
                                      reinterpret_cast<const int32_t*>(reinterpret_cast<uint8_t*>(suid) + shift),
                                      c->stream, ps.kt());
@@ -1611,7 +1605,7 @@ int a2t_dev_open(a2t_cache* c, int32_t n_streams, const int32_t* ids, const int3
     for (int i = 0; i < n_streams; ++i) a.ids[i] = ids[i];
     DeviceGuard dg(c->cfg.device);
     if (launch_dev_open(c->dev, a, n_rows, unit_id, seg, pos, c->dplan, c->stream) != hipSuccess ||
-        launch_step_meta_dev(c->dev, c->dplan, n_streams, seg, pos, unit_id, c->stream) != hipSuccess)
+        launch_step_meta_dev(c->dev, c->freq, c->dplan, n_streams, seg, pos, unit_id, c->stream) != hipSuccess)
         return hip_fail(c);
     c->dev_step_open = true;
     c->dev_count = n_streams;

@@ -62,8 +62,12 @@ struct DevState {
     int32_t G;          // query heads per KV head (Hq / Hkv)
     int32_t unit_rows, kept_rows, max_step_rows;
     float scale_log2e;  // softmax scale * log2(e)
-    double theta;
-    double* inv_freq;   // [D / 2] theta^(-2i/D)
+};
+
+// Rotary frequencies theta^(-2i/D) of a cache, a kernel argument of the step registration:
+// evaluated once, on the host, so that creating a cache enqueues nothing.
+struct RopeFreq {
+    double f[64];
 };
 
 __host__ __device__ inline int64_t pool_index(const DevState& st, int layer, int s, int g,
@@ -205,11 +209,9 @@ struct KTimer {
     hipEvent_t stop = nullptr;
 };
 
-// Fills st.inv_freq (once per cache).
-hipError_t launch_inv_freq(const DevState& st, hipStream_t stream);
 // Launchers (kernels.hip).  Each issues one kernel and returns the hipError_t
 // of the launch.
-hipError_t launch_step_meta(const DevState& st, const StepBatch& b, const uint8_t* seg,
+hipError_t launch_step_meta(const DevState& st, const RopeFreq& freq, const StepBatch& b, const uint8_t* seg,
                             const int32_t* pos, const int32_t* uid, hipStream_t stream,
                             const KTimer& kt);
 hipError_t launch_append(const DevState& st, const AppendBatch& b, int n_layers,
@@ -255,7 +257,7 @@ hipError_t launch_evict(const DevState& st, const EvictBatch& b, hipStream_t str
 hipError_t launch_dev_open(const DevState& st, const DevStepArgs& a, const int32_t* n_rows,
                            const int32_t* unit, const uint8_t* seg, const int32_t* pos,
                            DevPlan* plan, hipStream_t stream);
-hipError_t launch_step_meta_dev(const DevState& st, const DevPlan* plan, int count,
+hipError_t launch_step_meta_dev(const DevState& st, const RopeFreq& freq, const DevPlan* plan, int count,
                                 const uint8_t* seg, const int32_t* pos, const int32_t* unit,
                                 hipStream_t stream);
 hipError_t launch_attn_tile_dev(const DevState& st, const DevPlan* plan, int count,
