@@ -153,6 +153,7 @@ struct a2t_cache {
     int64_t plan_limit = -1;
     std::vector<int> plan_tiles, plan_splits, plan_tmp, plan_order;
     std::vector<int64_t> plan_heap;
+    SplitPlanner planner;            // of attn_block and attn_f32 launches
     bool force_valu = false;
     // profiling
     bool prof_on = false;
@@ -410,62 +411,35 @@ bool many_rows(const a2t_cache* c, int n, const int32_t* ids, const int32_t* n_q
            (G * rows > kBlockRows && tiles * c->cfg.n_kv_heads >= (int64_t)kBlockTilesPerCu * c->target_wgs);
 }
 
-// Key splits of an attn_block launch: none where its query blocks fill the CUs,
-// else the fewest tiles per split (at least kBlockMinTiles) whose workgroups
-// still fit one round.
-constexpr int kBlockMinTiles = 4;
-void plan_block_splits(const a2t_cache* c, int n, const int* tiles, const int32_t* n_q,
-                       const int64_t* floats_per_split, int* splits, int64_t ws_limit) {
-    const int Hkv = c->cfg.n_kv_heads, G = c->cfg.n_q_heads / Hkv;
-    int max_tiles = 1;
-    for (int i = 0; i < n; ++i) max_tiles = std::max(max_tiles, tiles[i]);
-    for (int budget = std::min(kBlockMinTiles, max_tiles); budget <= max_tiles; ++budget) {
-        int64_t wgs = 0, ws = 0;
-        for (int i = 0; i < n; ++i) {
-            const int want = c->force_splits > 0 ? std::min(c->force_splits, tiles[i]) : (tiles[i] + budget - 1) / budget;
-            splits[i] = std::max(1, std::min(want, kMaxSplits));
-            wgs += (int64_t)splits[i] * Hkv * ((G * n_q[i] + kBlockRows - 1) / kBlockRows);
-            ws += stream_partials(splits[i], floats_per_split[i]);
-        }
-        if ((wgs <= c->target_wgs || c->force_splits > 0) && ws <= ws_limit) return;
-    }
-    std::fill(splits, splits + n, 1);
-}
+// What attn_block's workgroups cost: a tile 0.7 to 1 us, the rest of one ~14, a merge launch
+// ~5 and as much again for 5 M floats of partials.  Measured at 1 to 16 splits (32/8 heads of
+// 128; us with 1, 2, 4 splits, merge included): five streams of 90 rows onto 2,000 keys 39.8,
+// 33.2, 41.2; eight of 65 rows 41.7, 63.0, 72.3; five of 256 rows onto 2,048 keys 83.7, 87.6,
+// 96.4; one of 65 rows and 15 of 22 rows onto 8,192 keys 150.0, 157.7, 141.6 (3 splits 126.6).
+constexpr SplitCosts kBlockCosts{16, 6, 1 << 20, 4, 0};
 
-// Key splits and query blocks per workgroup of an attn_f32 launch.
+// An attn_f32 launch: query blocks per workgroup, and what its workgroups cost.
 //
 // Two query blocks per workgroup halve the K and V that a launch fetches from L2 (2 streams
 // of ~2,100 keys, 88 query rows per KV head, 32/8 heads of 128: 26.5 against 31 us); one
 // where workgroups of two would leave most CUs idle (88 query rows of one KV head, 280 keys:
 // 9.5 against 12.6 us).
-// Streams of up to kF32WholeTiles tiles are not split: the merge costs more than the split
-// gains (the same 280 keys: 9.5 us against 7.6 + 3.9 with one).  Longer ones get the fewest
-// tiles per split (at least 2) whose workgroups fit one round over the CUs; two workgroups per
-// CU were slower (33 against 26.5 us).
-constexpr int kF32WholeTiles = 8;
-void plan_f32(const a2t_cache* c, int n, const int* tiles, const int32_t* n_q, const int64_t* floats_per_split,
-              int* splits, int* query_blocks, int64_t ws_limit) {
+// Launches whose streams have up to 8 tiles are not split: the merge costs more than the
+// splits gain (the same 280 keys: 9.5 us against 7.6 + 3.9).  Of longer ones a tile takes
+// 1.5 to 2.6 us (1 or 2 query blocks), a workgroup's rest ~12 and the merge ~5 (2 streams of
+// 2,022 keys and 22 rows, attention alone with 1, 2, 4, 5, 6, 8 splits: 100, 57, 36, 33, 46 (a
+// second round of workgroups), 43 us; 33 streams of 4,096 keys and one row with 1, 2, 4, 8:
+// 301, 256, 216, 214).
+constexpr SplitCosts kF32Costs{5, 2, 1 << 20, 2, 8};
+int f32_query_blocks(const a2t_cache* c, int n, const int* tiles, const int32_t* n_q) {
     const int Hkv = c->cfg.n_kv_heads, G = c->cfg.n_q_heads / Hkv;
-    int max_tiles = 1, max_rows = 1;
+    int max_rows = 1;
     int64_t pairs = 0;
     for (int i = 0; i < n; ++i) {
-        max_tiles = std::max(max_tiles, tiles[i]);
         max_rows = std::max(max_rows, G * n_q[i]);
-        pairs += (int64_t)Hkv * f32_groups(G * n_q[i], 2) * ((tiles[i] + kF32WholeTiles - 1) / kF32WholeTiles);
+        pairs += (int64_t)Hkv * f32_groups(G * n_q[i], 2) * ((tiles[i] + kF32Costs.whole - 1) / kF32Costs.whole);
     }
-    *query_blocks = max_rows > 16 && pairs * 2 >= c->target_wgs ? 2 : 1;
-    const bool force = c->force_splits > 0;
-    for (int budget = !force && max_tiles <= kF32WholeTiles ? max_tiles : std::min(2, max_tiles); budget <= max_tiles; ++budget) {
-        int64_t wgs = 0, ws = 0;
-        for (int i = 0; i < n; ++i) {
-            const int want = force ? std::min(c->force_splits, tiles[i]) : (tiles[i] + budget - 1) / budget;
-            splits[i] = std::max(1, std::min(want, kMaxSplits));
-            wgs += (int64_t)splits[i] * Hkv * f32_groups(G * n_q[i], *query_blocks);
-            ws += stream_partials(splits[i], floats_per_split[i]);
-        }
-        if ((wgs <= c->target_wgs || force) && ws <= ws_limit) return;
-    }
-    std::fill(splits, splits + n, 1);
+    return max_rows > 16 && pairs * 2 >= c->target_wgs ? 2 : 1;
 }
 
 // Where a launch's split partials go: the cache's workspace (default) or the
@@ -525,12 +499,19 @@ int attn_launch(a2t_cache* c, int layer, int n, const int32_t* ids, const int32_
         floats[i] = (int64_t)c->cfg.n_kv_heads * G * n_q[i] * rf;
     }
     const bool block = !in_row0 && many_rows(c, n, ids, n_q);
-    if (f32)
-        plan_f32(c, n, tiles, n_q, floats, nsplit, &query_blocks, wsc ? wsc->floats : c->dev.ws_floats);
-    else if (block)
-        plan_block_splits(c, n, tiles, n_q, floats, nsplit, wsc ? wsc->floats : c->dev.ws_floats);
-    else
+    if (f32 || block) {
+        SplitStream ss[kMaxDesc];
+        if (f32) query_blocks = f32_query_blocks(c, n, tiles, n_q);
+        for (int i = 0; i < n; ++i) {
+            const int rows = G * n_q[i];
+            ss[i] = {tiles[i], c->cfg.n_kv_heads * (f32 ? f32_groups(rows, query_blocks) : (rows + kBlockRows - 1) / kBlockRows),
+                     floats[i]};
+        }
+        c->planner.plan(n, ss, f32 ? kF32Costs : kBlockCosts, c->target_wgs, c->force_splits,
+                        wsc ? wsc->floats : c->dev.ws_floats, nsplit);
+    } else {
         plan_splits(c, n, tiles, floats, nsplit, wsc ? INT64_MAX : c->dev.ws_floats);
+    }
     // descriptors in order of falling tiles per split: the dispatcher starts the
     // longest workgroups first
     int ord[kMaxDesc];
@@ -757,6 +738,7 @@ int a2t_cache_create(const a2t_config* cfg, void* hip_stream, a2t_cache** out) {
     // the split planner's scratch, so that no attention call allocates
     for (auto* v : {&c->plan_tiles, &c->plan_splits, &c->plan_tmp, &c->plan_order}) v->reserve(kMaxDesc);
     c->plan_heap.reserve((size_t)c->target_wgs);
+    c->planner.reserve(kMaxDesc, c->target_wgs);
 
     DevState& d = c->dev;
     d.L = k.n_layers;
