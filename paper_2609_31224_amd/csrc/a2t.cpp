@@ -399,16 +399,35 @@ constexpr int kBlockTilesPerCu = 6;
 // below that attn_tile's key splits fill the GPU and the append's launch costs more
 // (132 query rows, one stream of 4,096 keys: 88 against 82 us; 4 tiles per CU: 127
 // against 124).
-bool many_rows(const a2t_cache* c, int n, const int32_t* ids, const int32_t* n_q) {
+//
+// Beside streams of one pass, which attn_tile reads at a fifth more bytes a second, the
+// streams of many passes may keep a launch there: a workgroup of attn_tile walks its passes
+// one after the other (a tile takes ~1.4 us, a pass besides it ~6, a tile of new rows, which
+// every pass rotates again, ~5), and as long as it ends with the others nothing is gained.
+// `extra` rows are added to each stream's resident count (a step that is about to be
+// appended).  Four layers of 32/8 heads of 128, attn_tile against attn_block: 100 rows onto
+// 100 keys beside 15 streams of 22 rows onto 8,192 keys 412 against 631 us, 65 rows beside 63
+// streams of one row onto ~2,900 keys 597 against 664; 70 rows beside 20 streams of 22 rows
+// onto ~2,300 keys 387 against 242.
+bool many_rows(const a2t_cache* c, int n, const int32_t* ids, const int32_t* n_q, const int32_t* extra = nullptr) {
     if (c->cfg.dtype != A2T_BF16 || c->force_valu) return false;
-    const int G = c->cfg.n_q_heads / c->cfg.n_kv_heads;
-    int64_t rows = 0, tiles = 0;   // row counts are not checked yet where an append follows
+    const int64_t G = c->cfg.n_q_heads / c->cfg.n_kv_heads, Hkv = c->cfg.n_kv_heads;
+    // in tiles; row counts are not checked yet where an append follows
+    int64_t rows = 0, tiles = 0, single = 0, chain = 0;
     for (int i = 0; i < n; ++i) {
+        const int64_t t = ((int64_t)c->ss[ids[i]].resident() + (extra ? extra[i] : 0) + kTileKeys - 1) / kTileKeys;
+        const int64_t passes = (G * n_q[i] + kBlockRows - 1) / kBlockRows;
         rows = std::max<int64_t>(rows, n_q[i]);
-        tiles += (c->ss[ids[i]].resident() + kTileKeys - 1) / kTileKeys;
+        tiles += t;
+        if (passes == 1) {
+            single += t;
+        } else {
+            const int64_t fresh = std::min(t, ((int64_t)n_q[i] + kTileKeys - 1) / kTileKeys);
+            chain = std::max(chain, passes * (4 + (t - fresh) + 7 * fresh / 2));
+        }
     }
-    return G * rows > 2 * kBlockRows ||
-           (G * rows > kBlockRows && tiles * c->cfg.n_kv_heads >= (int64_t)kBlockTilesPerCu * c->target_wgs);
+    if (single && 4 * chain <= 5 * single * Hkv / c->target_wgs + 28) return false;
+    return G * rows > 2 * kBlockRows || (G * rows > kBlockRows && tiles * Hkv >= (int64_t)kBlockTilesPerCu * c->target_wgs);
 }
 
 // What attn_block's workgroups cost: a tile 0.7 to 1 us, the rest of one ~14, a merge launch
@@ -1043,7 +1062,7 @@ int append_attn_impl(a2t_cache* c, int32_t layer, int32_t n_streams, const int32
     // query blocks would otherwise rotate the step's keys again
     bool fused = c->cfg.dtype == A2T_F32 || !c->force_valu;
     for (int i0 = 0; i0 < n_streams && fused; i0 += kMaxDesc)
-        fused = !many_rows(c, std::min(kMaxDesc, n_streams - i0), ids + i0, n_q + i0);
+        fused = !many_rows(c, std::min(kMaxDesc, n_streams - i0), ids + i0, n_q + i0, layer == 0 ? n_rows + i0 : nullptr);
     int rc = append_impl(c, layer, n_streams, ids, n_rows, kin, vin, seg, pos, unit_id, !fused);
     if (rc) return rc;
     if (!fused) return attn_common(c, layer, n_streams, ids, n_q, q, o, false, wsc);

@@ -134,3 +134,27 @@ def test_infinite_values(gpu, d, splits, monkeypatch):
     assert np.isposinf(outs[1][bad:, :, 0]).all()
     assert np.array_equal(outs[0][:, :, 1:], outs[1][:, :, 1:])
     assert np.array_equal(outs[0][:256, :, 0], outs[1][:256, :, 0])   # whole blocks of 128 query rows
+
+
+@pytest.mark.parametrize("target,tile,block", [("1", 4, 2), (None, 2, 4)])
+@pytest.mark.parametrize("fused", [False, True])
+def test_mixed_batch_routes(gpu, monkeypatch, target, tile, block, fused):
+    """A batch of one stream with several passes of query rows among streams of one pass: it
+    stays on attn_tile where the others fill the launch (here: one CU is counted) and runs on
+    attn_block where they do not, with the oracle's results on either.  Of the three steps the
+    first holds the other streams' prefixes, many rows each, and the last no long unit."""
+    import paper_2609_31224_amd as a2t
+    if target:
+        monkeypatch.setenv("A2T_TARGET_WGS", target)
+    cfg = dataclasses.replace(CONFIGS[0], n_q_heads=8, n_kv_heads=2, head_dim=128)
+    specs = []
+    for s, (rows, prefix) in enumerate(((90, 0), (20, 700), (22, 1000), (19, 850), (25, 900))):
+        specs.append(dataclasses.replace(tiny_stream([_long(rows), _long(rows)], prefix=prefix), stream=s))
+    ls = Lockstep(cfg, 9, specs, layers_checked=[0, 1], n_layers=2, budgets=[60, 2000, 2000, 2000, 2000], window=1,
+                  unit_rows=1100, kept_rows=64, max_step=1024, tol=BF16_TOL, dtype="bf16", fused=fused)
+    a2t.a2t_profile_enable(ls.cache, "")
+    try:
+        ls.run()
+        assert [a2t.a2t_kernel_time(ls.cache, n)[0] for n in ("attn_tile", "attn_block")] == [tile, block]
+    finally:
+        ls.close()
