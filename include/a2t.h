@@ -421,7 +421,8 @@ int a2t_sync(a2t_cache* c);
 /* Kernel timing with HIP events on the cache's stream (for benchmarks).
  * kernel_filter: NULL disables timing; "" times every kernel; otherwise only
  * kernels whose name contains the string ("step_meta", "append",
- * "attn_tile", "attn_block", "attn_f32", "attn_valu", "attn_merge", "evict").  While enabled, each
+ * "attn_tile", "attn_block", "attn_f32", "attn_f32x2" (attn_f32 with two query
+ * blocks per workgroup), "attn_valu", "attn_merge", "evict").  While enabled, each
  * matching launch carries a start/stop event pair recorded at the dispatch's
  * own begin and end.  a2t_kernel_time waits for the
  * stream, then reports for the kernels whose name contains `kernel` the

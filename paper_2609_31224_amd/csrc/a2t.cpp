@@ -621,7 +621,7 @@ int attn_launch(a2t_cache* c, int layer, int n, const int32_t* ids, const int32_
         return e == hipSuccess ? A2T_OK : hip_fail(c);
     }
     {
-        ProfScope ps(c, f32 ? "attn_f32" : valu ? "attn_valu" : block ? "attn_block" : "attn_tile");
+        ProfScope ps(c, f32 ? (query_blocks == 2 ? "attn_f32x2" : "attn_f32") : valu ? "attn_valu" : block ? "attn_block" : "attn_tile");
         e = launch(c->dev, ps.kt());
     }
     if (e != hipSuccess) return hip_fail(c);

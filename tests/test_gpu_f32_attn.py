@@ -87,3 +87,74 @@ def test_masked_values_stay_out(gpu, d, rows, bad):
     # the same sums in another order: a few roundings of a convex combination of |v| < 6
     assert np.abs(outs[0][:bad] - outs[1][:bad]).max(initial=0.0) < 1e-5
     assert np.isnan(outs[1][bad:]).all()
+
+
+def _lockstep(monkeypatch, hq, hkv, d, rows, prefix, splits, fused, query_rows):
+    """The long units of test_f32_chunks on workgroups of two query blocks (every launch of
+    more than 16 query rows asks for them where one CU is counted)."""
+    import paper_2609_31224_amd as a2t
+    monkeypatch.setenv("A2T_TARGET_WGS", "1")
+    monkeypatch.setenv("A2T_SPLITS", splits)
+    cfg = dataclasses.replace(CONFIGS[0], n_q_heads=hq, n_kv_heads=hkv, head_dim=d)
+    spec = tiny_stream([SMALL, _unit(rows), SMALL, _unit(rows), _unit(rows + 1), SMALL, _unit(rows), _unit(rows)], prefix=prefix)
+    bounds = row_bounds(spec)
+    ls = Lockstep(cfg, 5, [spec], layers_checked=[0, 1], n_layers=2, budgets=[prefix + rows + 20], window=0,
+                  unit_rows=2 * rows + 40 + prefix, kept_rows=bounds[1] + 1,
+                  max_step=max(bounds[2], rows + 1), tol=F32_TOL, dtype="f32", fused=fused, query_rows=query_rows)
+    a2t.a2t_profile_enable(ls.cache, "attn_f32")
+    try:
+        ls.run()
+        return ls, a2t.a2t_kernel_time(ls.cache, "attn_f32x2")[0], a2t.a2t_kernel_time(ls.cache, "attn_f32")[0]
+    finally:
+        ls.close()
+
+
+@pytest.mark.parametrize("splits", ["1", "3", "5"])
+@pytest.mark.parametrize("hq,hkv,d,rows,prefix,fused,query_rows", [
+    (17, 17, 64, 17, 30, True, None),      # one query head: the second block holds one row
+    (4, 1, 64, 33, 130, False, None),      # 132 query rows: an odd block, the last group half empty
+    (8, 2, 128, 40, 200, True, None),      # 160: whole groups
+    (8, 1, 128, 21, 70, True, 9),          # 72 of 168, the ring wraps between the queries' keys
+    (3, 3, 128, 50, 0, False, 35),
+])
+def test_f32_two_blocks(gpu, monkeypatch, hq, hkv, d, rows, prefix, splits, fused, query_rows):
+    """Groups of two query blocks over resident, wrapped and kept keys, with split partials."""
+    ls, two, one = _lockstep(monkeypatch, hq, hkv, d, rows, prefix, splits, fused, query_rows)
+    # two layers x the five long units (more than 16 query rows each) at least
+    assert two >= 10 and ls.evictions >= 3, (two, one, ls.evictions)
+    print(f"rows {rows}: max attention error {ls.max_err:.2e}, {two} of {two + one} launches of two blocks", flush=True)
+
+
+@pytest.mark.parametrize("splits", ["1", "3"])
+@pytest.mark.parametrize("d,rows,bad", [(64, 9, 5), (128, 22, 21), (128, 40, 17), (64, 33, 32)])
+def test_masked_values_stay_out_of_two_blocks(gpu, monkeypatch, d, rows, bad, splits):
+    """test_masked_values_stay_out on workgroups of two query blocks, onto resident rows."""
+    import torch
+    import paper_2609_31224_amd as a2t
+    monkeypatch.setenv("A2T_TARGET_WGS", "1")
+    monkeypatch.setenv("A2T_SPLITS", splits)
+    hq, hkv, old = 4, 2, 70
+    g = torch.Generator(device="cuda").manual_seed(3)
+    k0, v0 = (torch.randn((old, hkv, d), generator=g, device="cuda") for _ in range(2))
+    k, v, q = (torch.randn((rows, h, d), generator=g, device="cuda") for h in (hkv, hkv, hq))
+    outs = []
+    for spoil in (False, True):
+        vv, kk = v.clone(), k.clone()
+        if spoil:
+            vv[bad, :, 0::2] = float("inf")
+            vv[bad, :, 1::2] = float("nan")
+            kk[bad, :, 3] = float("nan")
+        c = a2t.a2t_cache_create(1, 1, hq, hkv, d, a2t.A2T_F32, old + 2 * rows, 8, max(old, rows))
+        o = torch.zeros_like(q)
+        a2t.a2t_append(c, 0, [0], [old], k0, v0, np.full(old, SEG_ACOUSTIC, np.uint8), np.arange(old), [0])
+        a2t.a2t_evict(c, [0], [10 * old], 1)
+        a2t.a2t_profile_enable(c, "attn_f32")
+        a2t.a2t_append_attn(c, 0, [0], [rows], kk, vv, np.full(rows, SEG_ACOUSTIC, np.uint8), np.arange(old, old + rows), [1],
+                            [rows], q, o)
+        a2t.a2t_sync(c)
+        assert a2t.a2t_kernel_time(c, "attn_f32x2")[0] == 1
+        outs.append(o.cpu().numpy())
+        a2t.a2t_cache_destroy(c)
+    # as in test_masked_values_stay_out
+    assert np.abs(outs[0][:bad] - outs[1][:bad]).max(initial=0.0) < 1e-5
+    assert np.isnan(outs[1][bad:]).all()
