@@ -45,14 +45,16 @@ constexpr float kLn2 = 0.693147180559945309417f;
 // ahead of the one it works on.
 template <typename T> struct Hold;
 
+// 20 bytes: a table of up to 16 KiB is copied by the runtime ~10 us faster than a larger one
+// (739 rows of 24 bytes: 18.6 -> 30.6 us a pass).
 struct DistillRow {
     int32_t row;        // row of the batch (rows are dispatched costliest first)
     int32_t target;     // ASR target, -1 elsewhere
-    float c_asr;        // weight of this row's CE in L_ASR
-    float c_nat;        // weight of this row's KL in L_native
+    float c_main;       // weight of this row's CE in L_ASR (target >= 0), else of its KL in L_native
     float c_dec;        // ... in L_dec
     float c_turn;       // ... in L_turn
 };
+static_assert(sizeof(DistillRow) == 20, "rows of the table");
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 struct bf16_t {
@@ -266,8 +268,8 @@ __global__ __launch_bounds__(kRowThreads) void distill_row_kernel(
     const T* s = student + (int64_t)r.row * s_stride;
     const T* t = teacher + (int64_t)r.row * t_stride;
     T* g = GRAD ? grad + (int64_t)r.row * s_stride : nullptr;
-    const float wk = r.c_nat + r.c_dec + r.c_turn;  // KL weight in the gradient
-    const float wc = r.c_asr;                       // CE weight in the gradient
+    const float wk = r.target < 0 ? r.c_main + r.c_dec + r.c_turn : 0.f;   // KL weight in the gradient
+    const float wc = r.target < 0 ? 0.f : r.c_main;                        // CE weight in the gradient
     const int nc = (vs + kChunk - 1) / kChunk, nt = (vocab + kChunk - 1) / kChunk;   // chunks
 
     if (wk == 0.f && wc == 0.f) {  // a row without loss: zero gradient
@@ -509,7 +511,7 @@ __global__ __launch_bounds__(kRowThreads) void distill_row_kernel(
     });
 }
 
-// one workgroup: sum_i c_asr ce_i, c_nat kl_i, c_dec kl_i, c_turn kl_i in a fixed order
+// one workgroup: sum_i c_main ce_i, c_main kl_i, c_dec kl_i, c_turn kl_i in a fixed order
 __global__ __launch_bounds__(kReduceThreads) void distill_reduce_kernel(const DistillRow* rows,
                                                                       const float2* rowval, int n,
                                                                       float* losses) {
@@ -518,8 +520,8 @@ __global__ __launch_bounds__(kReduceThreads) void distill_reduce_kernel(const Di
     for (int i = tid; i < n; i += kReduceThreads) {
         const DistillRow r = rows[i];
         const float2 v = rowval[i];
-        a += r.c_asr * v.x;
-        b += r.c_nat * v.y;
+        a += r.target < 0 ? 0.f : r.c_main * v.x;
+        b += r.target < 0 ? r.c_main * v.y : 0.f;
         c += r.c_dec * v.y;
         d += r.c_turn * v.y;
     }
@@ -698,12 +700,12 @@ extern "C" int a2t_distill_loss(a2t_distill* d, int32_t n_rows, const void* stud
     DistillRow* h = d->stage[slot];
     int at[3] = {(int)(n_nat + n_asr), (int)n_nat, 0};   // by kind: none, ASR, native
     for (int i = 0; i < n_rows; ++i) {
-        DistillRow r{i, -1, 0.f, 0.f, 0.f, 0.f};
+        DistillRow r{i, -1, 0.f, 0.f, 0.f};
         if (kind[i] == A2T_ROW_ASR) {
             r.target = target[i];
-            r.c_asr = (float)(1.0 / (double)n_asr);
+            r.c_main = (float)(1.0 / (double)n_asr);
         } else if (kind[i] == A2T_ROW_NATIVE) {
-            r.c_nat = (float)(1.0 / (double)n_nat);
+            r.c_main = (float)(1.0 / (double)n_nat);
             if (dec_group[i] >= 0) r.c_dec = (float)(1.0 / ((double)g_dec * n_dec[dec_group[i]]));
             if (turn_group[i] >= 0) r.c_turn = (float)(1.0 / ((double)g_turn * n_turn[turn_group[i]]));
         }
