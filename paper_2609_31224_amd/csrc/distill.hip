@@ -256,11 +256,11 @@ __device__ __forceinline__ void in_turn() { __builtin_amdgcn_sched_barrier(0); }
 // with one 256-thread workgroup per row that kept online maxima per chunk, read the
 // teacher of every row and read both again for the gradient: bound by ~75 vector
 // operations per logit); teacher re-read whole instead of from LDS: 231 us.
-template <typename T, bool GRAD>
+template <typename T, bool GRAD, int NR>
 __global__ __launch_bounds__(kRowThreads) void distill_row_kernel(
     const T* student, int64_t s_stride, const T* teacher, int64_t t_stride, int vocab, int vs,
     const DistillRow* rows, float inv_t, float2* rowval, T* grad) {
-    constexpr int NR = Hold<T>::kRegs, NL = Hold<T>::kLds;
+    constexpr int NL = NR < Hold<T>::kLds ? NR : Hold<T>::kLds;
     extern __shared__ u32x4 t_lds[];           // GRAD: NL chunks of the teacher per thread
     __shared__ float part[5 * kRowThreads / 64];
     const int tid = threadIdx.x, TH = blockDim.x;
@@ -370,7 +370,7 @@ __global__ __launch_bounds__(kRowThreads) void distill_row_kernel(
         // ---- native row: student and teacher at temperature T
         Sum u{-kFar, 0.f};
         SumA w{-kFar, 0.f, 0.f};
-        constexpr int NA = Hold<T>::kAhead;
+        constexpr int NA = NR - 1 < Hold<T>::kAhead ? NR - 1 : Hold<T>::kAhead;
         Raw<T> ts[NR];   // in flight: NA chunks ahead of the one in work
 #pragma unroll
         for (int k = 0; k < NA; ++k) ts[k] = teacher_chunk(chunk_no(k));
@@ -423,7 +423,8 @@ __global__ __launch_bounds__(kRowThreads) void distill_row_kernel(
                 if (c < nc) store_chunk(g, c, a);
             };
 #pragma unroll
-            for (int k = NL; k < NL + NA; ++k) ts[k] = teacher_chunk(chunk_no(k));
+            for (int k = NL; k < NL + NA; ++k)
+                if (k < NR) ts[k] = teacher_chunk(chunk_no(k));
 #pragma unroll
             for (int k = 0; k < NR; ++k) {
                 // the chunks that LDS holds are written while the others are on their way
@@ -581,11 +582,16 @@ struct DevGuard {
 // CU has several rows in different phases; more where the rows alone do not fill the
 // CUs' 1,024 threads each, as long as a thread keeps four chunks (252 rows of 32,005
 // fp32 logits: 20.7 us with 512 threads a row, 24.1 with 1,024, whose waves take
-// longer to start; 1,340 rows of 10,009 bf16 logits: 44.8 us with 128, 42.4 with 256).
+// longer to start; 1,340 rows of 10,009 bf16 logits: 44.8 us with 128, 42.4 with 256),
+// and one where they fill less than a quarter (row kernel alone, 27 rows of 3,502 bf16
+// logits: 8.3 us with 64 threads, 6.2 with 256; 1,355 of them: 10.3 with 64, 10.7).
 int row_threads(int n_rows, int chunks, int regs, int cus) {
     int th = 64;
+    const int64_t all = (int64_t)cus * kRowThreads;
     while (th < kRowThreads && th * regs < chunks) th *= 2;
-    while (th < kRowThreads && 8 * th <= chunks && (int64_t)n_rows * th < (int64_t)cus * kRowThreads) th *= 2;
+    while (th < kRowThreads && ((8 * th <= chunks && (int64_t)n_rows * th < all) ||
+                                (th < 256 && 2 * th <= chunks && 4LL * n_rows * th < all)))
+        th *= 2;
     return th;
 }
 void free_distill(a2t_distill* d) {
@@ -729,23 +735,33 @@ extern "C" int a2t_distill_loss(a2t_distill* d, int32_t n_rows, const void* stud
                 d->prof_free.pop_back();
             }
         }
-        auto go = [&](auto kernel, auto* logits, int regs) {
+        const int chunks = (vs + kChunk - 1) / kChunk;
+        auto go = [&](auto kernel, auto* logits, int th) {
             using T = std::remove_const_t<std::remove_pointer_t<decltype(logits)>>;
-            const int th = row_threads(n_rows, (vs + kChunk - 1) / kChunk, regs, d->cus);
             hipExtLaunchKernelGGL(kernel, dim3(n_rows), dim3(th), grad ? th * 128 : 0, d->stream, ev.first, ev.second, 0,
                                   static_cast<const T*>(student), student_stride, static_cast<const T*>(teacher),
                                   teacher_stride, d->vocab, vs, (const DistillRow*)d->rows_dev, inv_t, d->rowval_dev,
                                   static_cast<T*>(grad));
         };
-        if (d->dtype == A2T_F32) {
-            const float* x = nullptr;
-            if (grad) go(distill_row_kernel<float, true>, x, Hold<float>::kRegs);
-            else go(distill_row_kernel<float, false>, x, Hold<float>::kRegs);
-        } else {
-            const bf16_t* x = nullptr;
-            if (grad) go(distill_row_kernel<bf16_t, true>, x, Hold<bf16_t>::kRegs);
-            else go(distill_row_kernel<bf16_t, false>, x, Hold<bf16_t>::kRegs);
-        }
+        // the kernel whose threads have few rounds more than the row asks for, because every
+        // round is loaded and cut, used or not (row kernel alone, with gradient, 22 rows of 1,715
+        // bf16 logits: 10.6 us with 19 rounds, 7.1 with 4; 33 rows of 22,267: 16.5 with 19, 11.8
+        // with 8; branches around the rounds made the 19-round kernel spill)
+        auto sized = [&](auto* logits) {
+            using T = std::remove_const_t<std::remove_pointer_t<decltype(logits)>>;
+            constexpr int kRegs = Hold<T>::kRegs, kSome = kRegs > 8 + 4 ? 8 : 4;
+            const int th = row_threads(n_rows, chunks, kRegs, d->cus), rounds = (chunks + th - 1) / th;
+            auto pick = [&](auto with_grad) {
+                constexpr bool G = decltype(with_grad)::value;
+                if (rounds <= 4) go(distill_row_kernel<T, G, 4>, logits, th);
+                else if (rounds <= kSome) go(distill_row_kernel<T, G, kSome>, logits, th);
+                else go(distill_row_kernel<T, G, kRegs>, logits, th);
+            };
+            if (grad) pick(std::true_type{});
+            else pick(std::false_type{});
+        };
+        if (d->dtype == A2T_F32) sized((const float*)nullptr);
+        else sized((const bf16_t*)nullptr);
         e = hipGetLastError();
         if (ev.first) d->prof_pending.push_back(ev);
     }

@@ -113,3 +113,18 @@ def test_rows_of_the_lowest_value(gpu, dtype):
     student = b.student.copy()
     student[b.target >= 0] = low
     _check(type(b)(student, b.teacher, b.kind, b.target, b.dec_group, b.turn_group), vocab, added, dtype, 1.0)
+
+
+@pytest.mark.parametrize("dtype,logits,batch", [
+    ("bf16", 2 * 64 * 8, (2, 3)), ("f32", 2 * 64 * 8 - 1, (2, 3)),             # one workgroup size and the next
+    ("bf16", 4 * 256 * 8, (2, 3)), ("bf16", 4 * 256 * 8 + 1, (2, 3)),          # 4 rounds and 5, 256 threads
+    ("f32", 4 * 256 * 8, (2, 3)), ("f32", 4 * 256 * 8 + 1, (2, 3)),
+    ("bf16", 8 * 256 * 8 - 8, (2, 3)), ("bf16", 8 * 256 * 8 - 7, (2, 3)),      # 8 rounds of 256 threads, 4 of 512
+    ("bf16", 8 * 1024 * 8, (1, 2)), ("bf16", 8 * 1024 * 8 + 1, (1, 2)),        # 8 rounds and 9, 1,024 threads
+    ("bf16", 1500, (16, 12)), ("f32", 3500, (12, 12)),                         # many rows, few threads each
+])
+def test_rounds_of_a_row(gpu, dtype, logits, batch):
+    """Row lengths around those at which a row's kernel holds more chunks a thread, and short
+    rows in batches large and small."""
+    b = make_distill_batch(seed=27, n_utt=batch[0], units=batch[1], vocab=logits - 2, added=2, dtype=dtype)
+    _check(b, logits - 2, 2, dtype, 2.0)
