@@ -435,7 +435,7 @@ bool many_rows(const a2t_cache* c, int n, const int32_t* ids, const int32_t* n_q
 // 128; us with 1, 2, 4 splits, merge included): five streams of 90 rows onto 2,000 keys 39.8,
 // 33.2, 41.2; eight of 65 rows 41.7, 63.0, 72.3; five of 256 rows onto 2,048 keys 83.7, 87.6,
 // 96.4; one of 65 rows and 15 of 22 rows onto 8,192 keys 150.0, 157.7, 141.6 (3 splits 126.6).
-constexpr SplitCosts kBlockCosts{16, 6, 1 << 20, 4, 0};
+constexpr SplitCosts kBlockCosts{16, 6, 1 << 20, 4};
 
 // An attn_f32 launch: query blocks per workgroup, and what its workgroups cost.
 //
@@ -443,22 +443,26 @@ constexpr SplitCosts kBlockCosts{16, 6, 1 << 20, 4, 0};
 // of ~2,100 keys, 88 query rows per KV head, 32/8 heads of 128: 26.5 against 31 us); one
 // where workgroups of two would leave most CUs idle (88 query rows of one KV head, 280 keys:
 // 9.5 against 12.6 us).
-// Launches whose streams have up to 8 tiles are not split: the merge costs more than the
-// splits gain (the same 280 keys: 9.5 us against 7.6 + 3.9).  Of longer ones a tile takes
-// 1.5 to 2.6 us (1 or 2 query blocks), a workgroup's rest ~12 and the merge ~5 (2 streams of
-// 2,022 keys and 22 rows, attention alone with 1, 2, 4, 5, 6, 8 splits: 100, 57, 36, 33, 46 (a
-// second round of workgroups), 43 us; 33 streams of 4,096 keys and one row with 1, 2, 4, 8:
-// 301, 256, 216, 214).
-constexpr SplitCosts kF32Costs{5, 2, 1 << 20, 2, 8};
+constexpr int kF32PairTiles = 8;   // tiles of a stream that a workgroup is counted for there
 int f32_query_blocks(const a2t_cache* c, int n, const int* tiles, const int32_t* n_q) {
     const int Hkv = c->cfg.n_kv_heads, G = c->cfg.n_q_heads / Hkv;
     int max_rows = 1;
     int64_t pairs = 0;
     for (int i = 0; i < n; ++i) {
         max_rows = std::max(max_rows, G * n_q[i]);
-        pairs += (int64_t)Hkv * f32_groups(G * n_q[i], 2) * ((tiles[i] + kF32Costs.whole - 1) / kF32Costs.whole);
+        pairs += (int64_t)Hkv * f32_groups(G * n_q[i], 2) * ((tiles[i] + kF32PairTiles - 1) / kF32PairTiles);
     }
     return max_rows > 16 && pairs * 2 >= c->target_wgs ? 2 : 1;
+}
+
+// What attn_f32's workgroups cost: a tile 0.9 us (head dim 64) or 1.6 (128) with one query
+// block, ~2.6 with two, the rest of one 5 to 12 us, the merge launch ~5.  A stream of 5 tiles
+// is left whole (280 keys, head dim 64: 9.5 us against 7.6 + 3.9), one of 8 is not (8 query
+// heads over one of 128, one row onto 480 keys: 18.0 us against 9.6 + 4.4).  2 streams of 2,022 keys and 22 rows,
+// attention alone with 1, 2, 4, 5, 6, 8 splits: 100, 57, 36, 33, 46 (a second round of
+// workgroups), 43 us; 33 streams of 4,096 keys and one row with 1, 2, 4, 8: 301, 256, 216, 214.
+SplitCosts f32_costs(int head_dim, int query_blocks) {
+    return {5, (query_blocks == 2 ? 2 : 3) + (head_dim == 64 ? 2 : 0), 1 << 20, 2};
 }
 
 // Where a launch's split partials go: the cache's workspace (default) or the
@@ -526,7 +530,7 @@ int attn_launch(a2t_cache* c, int layer, int n, const int32_t* ids, const int32_
             ss[i] = {tiles[i], c->cfg.n_kv_heads * (f32 ? f32_groups(rows, query_blocks) : (rows + kBlockRows - 1) / kBlockRows),
                      floats[i]};
         }
-        c->planner.plan(n, ss, f32 ? kF32Costs : kBlockCosts, c->target_wgs, c->force_splits,
+        c->planner.plan(n, ss, f32 ? f32_costs(c->cfg.head_dim, query_blocks) : kBlockCosts, c->target_wgs, c->force_splits,
                         wsc ? wsc->floats : c->dev.ws_floats, nsplit);
     } else {
         plan_splits(c, n, tiles, floats, nsplit, wsc ? INT64_MAX : c->dev.ws_floats);

@@ -41,7 +41,6 @@ struct SplitCosts {
     int merge;       // of the merge launch that splits need,
     int64_t merge_floats;   // one more for so many floats of partials
     int min_tiles;   // fewest tiles worth a workgroup
-    int whole;       // launches whose streams have at most this many tiles are not split
 };
 
 class SplitPlanner {
@@ -58,7 +57,8 @@ public:
     // force > 0: that many splits (bounded by a stream's tiles) wherever they fit
     void plan(int n, const SplitStream* s, const SplitCosts& costs, int slots, int force, int64_t ws_limit, int* splits) {
         // every layer of a step plans the same launch
-        if (force == force_ && ws_limit == limit_ && slots == slots_ && costs.fixed == fixed_ && (int)last_.size() == n &&
+        if (force == force_ && ws_limit == limit_ && slots == slots_ && costs.fixed == costs_.fixed && costs.merge == costs_.merge && costs.merge_floats == costs_.merge_floats &&
+            costs.min_tiles == costs_.min_tiles && (int)last_.size() == n &&
             std::equal(s, s + n, last_.begin())) {
             std::copy(splits_.begin(), splits_.end(), splits);
             return;
@@ -73,7 +73,7 @@ public:
                 ws += stream_partials(splits_[i], s[i].floats);
             }
             if (ws > ws_limit) splits_.assign(n, 1);
-        } else if (max_tiles > costs.whole) {
+        } else {
             try_.resize(n);
             int64_t best = INT64_MAX, best_wgs = 0;
             // budgets a sixteenth apart; the last one splits nothing
@@ -98,7 +98,7 @@ public:
             }
         }
         last_.assign(s, s + n);
-        force_ = force, limit_ = ws_limit, slots_ = slots, fixed_ = costs.fixed;
+        force_ = force, limit_ = ws_limit, slots_ = slots, costs_ = costs;
         std::copy(splits_.begin(), splits_.end(), splits);
     }
 
@@ -137,7 +137,8 @@ private:
     std::vector<SplitStream> last_;
     std::vector<int> splits_, order_, try_;
     std::vector<std::pair<int64_t, int64_t>> levels_;
-    int force_ = -1, slots_ = -1, fixed_ = -1;
+    SplitCosts costs_{};
+    int force_ = -1, slots_ = -1;
     int64_t limit_ = -1;
 };
 

@@ -14,15 +14,15 @@ MAIN = r"""
 #include "split_plan.h"
 #include <cstdio>
 #include <cstdlib>
-// a plan a line: slots force ws_limit fixed merge merge_floats min_tiles whole n {tiles wgs floats}
+// a plan a line: slots force ws_limit fixed merge merge_floats min_tiles n {tiles wgs floats}
 int main() {
     a2t::SplitPlanner p;
     p.reserve(64, 256);
     int slots, force, n;
     long long limit, mf;
     a2t::SplitCosts c;
-    while (std::scanf("%d %d %lld %d %d %lld %d %d %d", &slots, &force, &limit, &c.fixed, &c.merge, &mf, &c.min_tiles,
-                      &c.whole, &n) == 9) {
+    while (std::scanf("%d %d %lld %d %d %lld %d %d", &slots, &force, &limit, &c.fixed, &c.merge, &mf, &c.min_tiles,
+                      &n) == 8) {
         c.merge_floats = mf;
         a2t::SplitStream s[64];
         int out[64];
@@ -38,8 +38,8 @@ int main() {
     }
 }
 """
-BLOCK = dict(fixed=16, merge=6, merge_floats=1 << 20, min_tiles=4, whole=0)
-F32 = dict(fixed=5, merge=2, merge_floats=1 << 20, min_tiles=2, whole=8)
+BLOCK = dict(fixed=16, merge=6, merge_floats=1 << 20, min_tiles=4)
+F32 = dict(fixed=5, merge=3, merge_floats=1 << 20, min_tiles=2)
 
 
 @pytest.fixture(scope="module")
@@ -56,7 +56,7 @@ def plan(tmp_path_factory):
     def run(asked):
         """[(streams [(tiles, wgs, floats)], costs, slots, force, limit)] -> [(makespan, splits)]"""
         text = "\n".join(
-            f"{slots} {force} {limit} {c['fixed']} {c['merge']} {c['merge_floats']} {c['min_tiles']} {c['whole']} {len(s)} "
+            f"{slots} {force} {limit} {c['fixed']} {c['merge']} {c['merge_floats']} {c['min_tiles']} {len(s)} "
             + " ".join("%d %d %d" % x for x in s) for s, c, slots, force, limit in asked)
         out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.split("\n")
         return [(int(a.split()[0]), [int(x) for x in a.split()[1:]]) for a in out if a]
@@ -101,9 +101,6 @@ def test_plans_hold(plan):
             assert splits == (want if sum(_partials(k, f) for k, (_, _, f) in zip(want, streams)) <= limit else [1] * len(streams))
             continue
         longest = max(t for t, _, _ in streams)
-        if longest <= c["whole"]:
-            assert max(splits) == 1
-            continue
         mine = span + (c["merge"] + partials // c["merge_floats"] if max(splits) > 1 else 0)
         for budget in sorted({min(longest, b) for b in (c["min_tiles"], 5, 8, 13, 16, longest)}):
             other = [min(-(-t // budget), MAX_SPLITS) for t, _, _ in streams]
