@@ -465,6 +465,19 @@ SplitCosts f32_costs(int head_dim, int query_blocks) {
     return {5, (query_blocks == 2 ? 2 : 3) + (head_dim == 64 ? 2 : 0), 1 << 20, 2};
 }
 
+// Whether an fp32 launch of one query row per KV head, already appended, runs on the vector
+// kernel, whose plan is given: a matrix product would fill one of its 16 query columns, and
+// what its workgroups do besides it takes longer.  Without splits it is the faster one (heads
+// of 128: 64 streams of 8 heads onto 100 keys 16.6 against 22.4 us, onto 1,500 136 against 150;
+// of 64: onto 500 28.2 against 32.9, onto 1,500 86.2 against 78.7); with splits at heads of 128
+// and long streams (16 streams of 8 heads, merge included: 500 keys 24 against 27.5 us, 300 25
+// against 19.7; at 64, 500 keys 22.1 against 18.4).
+bool f32_on_valu(int head_dim, int n, const int* tiles, const int* splits) {
+    const int longest = *std::max_element(tiles, tiles + n);
+    const bool whole = *std::max_element(splits, splits + n) == 1;
+    return head_dim == 128 ? whole || longest > 6 : whole && longest <= 16;
+}
+
 // Where a launch's split partials go: the cache's workspace (default) or the
 // library's fixed device array (the no-allocation entry point, which plans
 // without the workspace limit and never times its launches).
@@ -510,7 +523,7 @@ int attn_launch(a2t_cache* c, int layer, int n, const int32_t* ids, const int32_
     // bf16 caches use the MFMA kernel for decode too: with one query row per
     // stream it is still bound by streaming the resident K/V, and its staged
     // tile pipeline keeps more bytes in flight than the VALU kernel.
-    const bool f32 = c->cfg.dtype == A2T_F32, valu = !f32 && c->force_valu;
+    bool f32 = c->cfg.dtype == A2T_F32, valu = !f32 && c->force_valu;
     const int64_t rf = partial_row_floats(c->cfg.head_dim, f32 || valu);
     int query_blocks = 1;
     int max_rows = 0, tiles[kMaxDesc], nsplit[kMaxDesc];
@@ -522,7 +535,14 @@ int attn_launch(a2t_cache* c, int layer, int n, const int32_t* ids, const int32_
         floats[i] = (int64_t)c->cfg.n_kv_heads * G * n_q[i] * rf;
     }
     const bool block = !in_row0 && many_rows(c, n, ids, n_q);
-    if (f32 || block) {
+    if (f32 && !in_row0 && !wsc && G == 1 && max_rows == 1) {
+        plan_splits(c, n, tiles, floats, nsplit, c->dev.ws_floats);
+        valu = f32_on_valu(c->cfg.head_dim, n, tiles, nsplit);
+        f32 = !valu;
+    }
+    if (valu && !c->force_valu) {
+        // planned above
+    } else if (f32 || block) {
         SplitStream ss[kMaxDesc];
         if (f32) query_blocks = f32_query_blocks(c, n, tiles, n_q);
         for (int i = 0; i < n; ++i) {

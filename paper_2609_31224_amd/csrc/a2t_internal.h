@@ -229,7 +229,7 @@ hipError_t launch_attn_block(const DevState& st, const AttnBatch& b, const void*
 // 2) blocks of 16 query rows per workgroup; with k_in/v_in non-null it also appends, like launch_attn_tile.  Split partials as launch_attn_valu's.
 hipError_t launch_attn_f32(const DevState& st, const AttnBatch& b, int query_blocks, const void* q, void* o,
                            const void* k_in, const void* v_in, hipStream_t stream, const KTimer& kt);
-// VALU attention of bf16 caches, one (row, kv head) per workgroup column.
+// VALU attention, one (row, kv head) per workgroup column (fp32 caches: one query head per KV head).
 hipError_t launch_attn_valu(const DevState& st, const AttnBatch& b, const void* q, void* o,
                             hipStream_t stream, const KTimer& kt);
 // h16: the partials come from the MFMA kernel (fp16 O rows), else from the VALU kernel (fp32)

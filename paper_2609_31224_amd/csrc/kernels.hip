@@ -12,7 +12,8 @@
 //               shuffles, key splits for parallelism; also bf16 decode (one
 //               query row per stream).
 //   attn_valu   the same attention on the vector ALU, one query row per
-//               workgroup column (bf16 caches under A2T_FORCE_VALU).
+//               workgroup column: fp32 decode with one query head per KV head
+//               (and bf16 caches under A2T_FORCE_VALU).
 //   attn_merge  combines key-split partials (fixed order, deterministic): split
 //               groups combined in LDS, or one thread per row walking every
 //               split when a launch's streams have few splits.
@@ -1582,7 +1583,16 @@ static hipError_t valu_dispatch_g(const DevState& st, const B& b, const void* q,
 hipError_t launch_attn_valu(const DevState& st, const AttnBatch& b, const void* q, void* o,
                             hipStream_t stream, const KTimer& kt) {
     return by_size<AttnBatchT>(b, [&](const auto& bb) {
-        if (st.dtype != 1) return hipErrorInvalidValue;
+        using B = std::decay_t<decltype(bb)>;
+        if (st.dtype == 0) {   // one query head per KV head
+            const dim3 grid(bb.max_splits, st.Hkv * bb.max_rows, bb.count);
+            const float* qq = static_cast<const float*>(q);
+            float* oo = static_cast<float*>(o);
+            if (st.Hq != st.Hkv || (st.D != 64 && st.D != 128)) return hipErrorInvalidValue;
+            if (st.D == 128) A2T_DISPATCH((attn_valu_kernel<float, 128, 1, B>), grid, dim3(256), stream, kt, st, bb, qq, oo);
+            else A2T_DISPATCH((attn_valu_kernel<float, 64, 1, B>), grid, dim3(256), stream, kt, st, bb, qq, oo);
+            return hipGetLastError();
+        }
         if (st.D == 128) return valu_dispatch_g<bf16_t, 128>(st, bb, q, o, stream, kt);
         if (st.D == 64) return valu_dispatch_g<bf16_t, 64>(st, bb, q, o, stream, kt);
         return hipErrorInvalidValue;

@@ -12,7 +12,7 @@ import os
 import numpy as np
 import pytest
 
-from synth.streams import CONFIGS, SEG_ACOUSTIC, SEG_DELIM, SEG_TEXT, tiny_stream
+from synth.streams import CONFIGS, SEG_ACOUSTIC, SEG_DELIM, SEG_RESPONSE, SEG_TEXT, tiny_stream
 from tests.harness import Lockstep, row_bounds
 
 pytestmark = pytest.mark.gpu
@@ -158,3 +158,29 @@ def test_masked_values_stay_out_of_two_blocks(gpu, monkeypatch, d, rows, bad, sp
     # as in test_masked_values_stay_out
     assert np.abs(outs[0][:bad] - outs[1][:bad]).max(initial=0.0) < 1e-5
     assert np.isnan(outs[1][bad:]).all()
+
+
+@pytest.mark.parametrize("hkv,d,prefix,splits,valu", [
+    (1, 64, 0, None, True), (1, 64, 60, None, True),      # one and two tiles: no splits
+    (3, 128, 0, None, True), (3, 128, 200, None, False),  # four tiles, split
+    (3, 128, 500, None, True),                            # eight tiles of 128 dims, split
+    (2, 64, 300, "1", True), (2, 64, 300, "3", False),
+    (2, 64, 1024, "1", False),                            # 17 tiles of 64 dims
+])
+def test_f32_one_query_row(gpu, monkeypatch, hkv, d, prefix, splits, valu):
+    """Decode rows with one query head per KV head: on the vector kernel where it is the faster
+    one, on attn_f32 elsewhere, the oracle's results on both."""
+    import paper_2609_31224_amd as a2t
+    if splits:
+        monkeypatch.setenv("A2T_SPLITS", splits)
+    cfg = dataclasses.replace(CONFIGS[0], n_q_heads=hkv, n_kv_heads=hkv, head_dim=d)
+    spec = tiny_stream([SMALL, [SEG_RESPONSE], [SEG_RESPONSE], SMALL, [SEG_RESPONSE], SMALL, [SEG_RESPONSE]], prefix=prefix)
+    bounds = row_bounds(spec)
+    ls = Lockstep(cfg, 5, [spec], layers_checked=[0, 1], n_layers=2, budgets=[prefix + 20], window=0,
+                  unit_rows=prefix + 40, kept_rows=bounds[1] + 1, max_step=bounds[2], tol=F32_TOL, dtype="f32")
+    a2t.a2t_profile_enable(ls.cache, "attn")
+    try:
+        ls.run()
+        assert a2t.a2t_kernel_time(ls.cache, "attn_valu")[0] == (8 if valu else 0)
+    finally:
+        ls.close()
