@@ -227,9 +227,9 @@ int a2t_chunk_attn(a2t_cache* c, int32_t layer, int32_t n_streams, const int32_t
                    const int32_t* n_q, const void* q, void* o);
 
 /* a2t_append on one layer followed by a2t_chunk_attn on that layer, in one
- * launch where the kernels allow it (bf16 caches): the workgroups whose key
- * tiles hold the step's new rows rotate and store them while staging them
- * for attention.  Arguments as in the two calls (layer 0..L-1 only; n_q
+ * launch where the kernels allow it (fp32 caches; bf16 caches except for steps
+ * of many query rows): the workgroups whose key tiles hold the step's new rows
+ * rotate and store them while staging them for attention.  Arguments as in the two calls (layer 0..L-1 only; n_q
  * host [n_streams] with 1 <= n_q <= n_rows; q and o packed [sum n_q][Hq][D]).
  * Results and cache contents are the same as the two calls. */
 int a2t_append_attn(a2t_cache* c, int32_t layer, int32_t n_streams, const int32_t* stream_ids,
@@ -242,14 +242,17 @@ int a2t_append_attn(a2t_cache* c, int32_t layer, int32_t n_streams, const int32_
  * arguments, results and cache contents as a2t_append_attn; the key-split
  * partials go to a fixed 16 MiB device array of the library (one per GPU, held
  * until the process ends) instead of the cache's workspace, so it also works
- * on a cache created with A2T_FLAG_NO_WORKSPACE.  Splits are planned as
- * a2t_append_attn plans them without a workspace limit; a call whose launch
- * would write more than 16 MiB of partials (4,194,304 floats; a stream's
+ * on a cache created with A2T_FLAG_NO_WORKSPACE.  What a call may ask for is
+ * judged by one plan, whichever kernel the launch then runs: key splits chosen
+ * for the resident rows alone, as a2t_append_attn plans an ordinary step, with no
+ * workspace limit.  A call for which that plan would write more than 16 MiB of
+ * partials (4,194,304 floats; a stream's
  * partials are splits x n_q x n_q_heads x (head_dim / 2 + 2) floats for a bf16
  * cache, fp16 output rows with an fp32 maximum and sum, and x (head_dim + 2)
  * for an fp32 cache: about 4 MiB for 22 query rows x 32 heads x head dim 128
  * at ~4,100 resident rows, 23 splits) is
- * rejected with A2T_ERR_CAPACITY before anything changes.  Every call on a GPU
+ * rejected with A2T_ERR_CAPACITY before anything changes.  Launches of an fp32
+ * cache or of many query rows may plan fewer splits, always within the array.  Every call on a GPU
  * shares that GPU's array: calls that overlap on one GPU (two caches on
  * different streams, or two host threads) race and must be serialised by the
  * caller; calls in order on one stream are safe.  Its launches are never timed

@@ -486,9 +486,11 @@ struct WsChoice {
     int64_t floats;
 };
 
-// Floats of split partials one launch over these streams writes at the
-// planner's choice (ws_limit as in plan_splits); `extra` rows are added to each
-// stream's resident count (a step that is about to be appended).
+// Floats of split partials one launch over these streams writes at the choice of
+// attn_tile's planner (ws_limit as in plan_splits), by which the no-allocation call
+// admits steps of every kernel: the launches of attn_block and attn_f32 plan within the
+// array by themselves.  `extra` rows are added to each stream's resident count (a step
+// that is about to be appended).
 int64_t planned_partials(a2t_cache* c, int n, const int32_t* ids, const int32_t* n_q,
                          const int32_t* extra, int64_t ws_limit) {
     const int G = c->cfg.n_q_heads / c->cfg.n_kv_heads;
@@ -511,7 +513,7 @@ int64_t planned_partials(a2t_cache* c, int n, const int32_t* ids, const int32_t*
 static bool unaligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; }
 
 // One attention launch (plus merge) over up to kMaxDesc streams.
-// With in_row0 non-null (bf16 MFMA path only) the launch also appends each
+// With in_row0 non-null (attn_tile and attn_f32) the launch also appends each
 // stream's open-step rows of `layer` from k_in / v_in.
 int attn_launch(a2t_cache* c, int layer, int n, const int32_t* ids, const int32_t* n_q,
                 const int32_t* q_row0, const void* q, void* o, const int32_t* in_row0 = nullptr, const void* k_in = nullptr,

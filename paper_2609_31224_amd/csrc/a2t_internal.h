@@ -201,6 +201,14 @@ inline BT<N> shrink_batch(const BT<kMaxDesc>& b) {
     return s;
 }
 
+// Calls f with the batch shrunk to the smallest of 1, 8 or kMaxDesc descriptors.
+template <template <int> class BT, class F>
+hipError_t by_size(const BT<kMaxDesc>& b, F&& f) {
+    if (b.count <= 1) return f(shrink_batch<BT, 1>(b));
+    if (b.count <= 8) return f(shrink_batch<BT, 8>(b));
+    return f(b);
+}
+
 // Optional dispatch timestamps: with start non-null the launcher issues its one
 // kernel through hipExtLaunchKernel, which records start/stop at the kernel's
 // own begin and end (no extra packets on the stream between them).

@@ -424,13 +424,6 @@ __global__ __launch_bounds__(kBlockThreads) void attn_block_kernel(DevState st, 
         store([](float x, float y) { return pack_bf16x2(x, y); });
 }
 
-template <template <int> class BT, class F>
-hipError_t by_size(const BT<kMaxDesc>& b, F&& f) {
-    if (b.count <= 1) return f(shrink_batch<BT, 1>(b));
-    if (b.count <= 8) return f(shrink_batch<BT, 8>(b));
-    return f(b);
-}
-
 }  // namespace
 
 hipError_t launch_attn_block(const DevState& st, const AttnBatch& b, const void* q, void* o, hipStream_t stream,

@@ -439,13 +439,6 @@ __global__ __launch_bounds__(64 * kKeyWaves, 2) void attn_f32_kernel(DevState st
     }
 }
 
-template <template <int> class BT, class F>
-hipError_t by_size(const BT<kMaxDesc>& b, F&& f) {
-    if (b.count <= 1) return f(shrink_batch<BT, 1>(b));
-    if (b.count <= 8) return f(shrink_batch<BT, 8>(b));
-    return f(b);
-}
-
 }  // namespace
 
 hipError_t launch_attn_f32(const DevState& st, const AttnBatch& b, int query_blocks, const void* q, void* o,

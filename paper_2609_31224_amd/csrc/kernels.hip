@@ -1502,14 +1502,6 @@ hipError_t static_scratch(int device, float** ptr, int64_t* floats) {
             hipLaunchKernelGGL(kernel, grid, block, 0, stream, __VA_ARGS__);                      \
     } while (0)
 
-// Calls f with the batch shrunk to the smallest of 1, 8 or kMaxDesc descriptors.
-template <template <int> class BT, class F>
-static hipError_t by_size(const BT<kMaxDesc>& b, F&& f) {
-    if (b.count <= 1) return f(shrink_batch<BT, 1>(b));
-    if (b.count <= 8) return f(shrink_batch<BT, 8>(b));
-    return f(b);
-}
-
 hipError_t launch_step_meta(const DevState& st, const RopeFreq& freq, const StepBatch& b, const uint8_t* seg,
                             const int32_t* pos, const int32_t* uid, hipStream_t stream,
                             const KTimer& kt) {
