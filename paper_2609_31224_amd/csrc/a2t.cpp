@@ -1559,7 +1559,8 @@ int a2t_dev_begin(a2t_cache* c) {
     DeviceGuard dg(c->cfg.device);
     if (hipStreamSynchronize(c->stream) != hipSuccess ||
         hipMemcpy(c->dev.dss, c->dss_host.data(), sizeof(DevStream) * c->dss_host.size(),
-                  hipMemcpyHostToDevice) != hipSuccess)
+                  hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(&c->dplan->freq, &c->freq, sizeof(RopeFreq), hipMemcpyHostToDevice) != hipSuccess)
         return hip_fail(c);
     c->dev_mode = true;
     c->dev_step_open = false;
@@ -1632,7 +1633,7 @@ int a2t_dev_open(a2t_cache* c, int32_t n_streams, const int32_t* ids, const int3
     for (int i = 0; i < n_streams; ++i) a.ids[i] = ids[i];
     DeviceGuard dg(c->cfg.device);
     if (launch_dev_open(c->dev, a, n_rows, unit_id, seg, pos, c->dplan, c->stream) != hipSuccess ||
-        launch_step_meta_dev(c->dev, c->freq, c->dplan, n_streams, seg, pos, unit_id, c->stream) != hipSuccess)
+        launch_step_meta_dev(c->dev, c->dplan, n_streams, seg, pos, unit_id, c->stream) != hipSuccess)
         return hip_fail(c);
     c->dev_step_open = true;
     c->dev_count = n_streams;

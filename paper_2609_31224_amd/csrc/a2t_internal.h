@@ -64,10 +64,15 @@ struct DevState {
     float scale_log2e;  // softmax scale * log2(e)
 };
 
-// Rotary frequencies theta^(-2i/D) of a cache, a kernel argument of the step registration:
-// evaluated once, on the host, so that creating a cache enqueues nothing.
+// Rotary frequencies theta^(-2i/D) of a cache: evaluated once, on the host, so that creating
+// a cache enqueues nothing.  Host-planned steps pass them as a kernel argument (they read
+// host memory anyway), device-planned ones read the copy that a2t_dev_begin puts in the plan
+// (a launch of two sessions' 44 rows 3.6 us; 4.9 with the argument).
 struct RopeFreq {
     double f[64];
+};
+struct RopeFreqPtr {
+    const double* f;
 };
 
 __host__ __device__ inline int64_t pool_index(const DevState& st, int layer, int s, int g,
@@ -175,6 +180,7 @@ struct DevBatch {
 // What a device-planned step's kernels read: written by dev_open_kernel
 // (metadata, attention) and dev_evict_plan_kernel (eviction).
 struct DevPlan {
+    RopeFreq freq;
     StepDesc step[kMaxDesc];
     AttnDesc attn[kMaxDesc];
     EvictDesc evict[kMaxDesc];
@@ -259,7 +265,7 @@ hipError_t launch_evict(const DevState& st, const EvictBatch& b, hipStream_t str
 hipError_t launch_dev_open(const DevState& st, const DevStepArgs& a, const int32_t* n_rows,
                            const int32_t* unit, const uint8_t* seg, const int32_t* pos,
                            DevPlan* plan, hipStream_t stream);
-hipError_t launch_step_meta_dev(const DevState& st, const RopeFreq& freq, const DevPlan* plan, int count,
+hipError_t launch_step_meta_dev(const DevState& st, const DevPlan* plan, int count,
                                 const uint8_t* seg, const int32_t* pos, const int32_t* unit,
                                 hipStream_t stream);
 hipError_t launch_attn_tile_dev(const DevState& st, const DevPlan* plan, int count,

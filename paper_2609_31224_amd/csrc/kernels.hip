@@ -114,8 +114,8 @@ __device__ __forceinline__ void copy8(bf16_t* d, const bf16_t* s) {
 // grid (row, stream): one workgroup per new row, one thread per rotary pair.  With the
 // frequencies' fp64 power left out and all loads requested together a launch takes 4.2 us
 // instead of 6.0 (22 rows).
-template <class BT>
-__global__ __launch_bounds__(64) void step_meta_kernel(DevState st, RopeFreq freq, BT b,
+template <class FT, class BT>
+__global__ __launch_bounds__(64) void step_meta_kernel(DevState st, FT freq, BT b,
                                                        const uint8_t* seg, const int32_t* pos,
                                                        const int32_t* uid) {
     const StepDesc d = b.d[blockIdx.y];
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(64) void step_meta_kernel(DevState st, RopeFreq fre
     // the staged arrays are host memory: everything is requested before any of it is used
     const int p = pos[d.row0 + r], u = uid[blockIdx.y];
     const int sg = seg[d.row0 + r];
-    const double inv = freq.f[i];
+    const double inv = freq.f[min(i, half - 1)];
     asm volatile("" ::"v"(p), "v"(u), "v"(sg), "v"(inv));
     if (i == 0) {
         int slot = d.slot0 + r;
@@ -1507,7 +1507,7 @@ hipError_t launch_step_meta(const DevState& st, const RopeFreq& freq, const Step
                             const KTimer& kt) {
     return by_size<StepBatchT>(b, [&](const auto& bb) {
         using B = std::decay_t<decltype(bb)>;
-        A2T_DISPATCH((step_meta_kernel<B>), dim3(b.max_n, b.count), dim3(64), stream, kt, st, freq, bb,
+        A2T_DISPATCH((step_meta_kernel<RopeFreq, B>), dim3(b.max_n, b.count), dim3(64), stream, kt, st, freq, bb,
                            seg, pos, uid);
         return hipGetLastError();
     });
@@ -1638,11 +1638,12 @@ hipError_t launch_dev_open(const DevState& st, const DevStepArgs& a, const int32
     return hipGetLastError();
 }
 
-hipError_t launch_step_meta_dev(const DevState& st, const RopeFreq& freq, const DevPlan* plan, int count,
+hipError_t launch_step_meta_dev(const DevState& st, const DevPlan* plan, int count,
                                 const uint8_t* seg, const int32_t* pos, const int32_t* unit,
                                 hipStream_t stream) {
     const DevBatch<StepDesc> b{{plan->step}, 0, 0};
-    hipLaunchKernelGGL((step_meta_kernel<DevBatch<StepDesc>>), dim3(st.max_step_rows, count),
+    const RopeFreqPtr freq{plan->freq.f};
+    hipLaunchKernelGGL((step_meta_kernel<RopeFreqPtr, DevBatch<StepDesc>>), dim3(st.max_step_rows, count),
                        dim3(64), 0, stream, st, freq, b, seg, pos, unit);
     return hipGetLastError();
 }
