@@ -316,6 +316,18 @@ class Runner:
 
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "attn_traffic.md")
 KERNEL_SOURCE = os.path.join(ROOT, "paper_2609_31224_amd", "csrc", "kernels.hip")
+# what the profiled kernels compile in besides
+KERNEL_HEADERS = [os.path.join(ROOT, "paper_2609_31224_amd", "csrc", f) for f in ("device_common.h", "a2t_internal.h")]
+
+
+def kernel_sha256():
+    """Hash of the profiled kernels' source and of the headers it includes, one after the other."""
+    import hashlib
+    sha = hashlib.sha256()
+    for path in [KERNEL_SOURCE, *KERNEL_HEADERS]:
+        with open(path, "rb") as f:
+            sha.update(f.read())
+    return sha.hexdigest()
 
 
 def measured_traffic(workload, kernel, units=None):
@@ -324,11 +336,10 @@ def measured_traffic(workload, kernel, units=None):
     copy's readings), or None when the summary was taken on other kernel
     source than the one built here, or (with ``units``) over other steps than
     the ones timed now."""
-    import hashlib
     import re
     try:
         text = open(TRAFFIC_PROFILE).read()
-        sha = hashlib.sha256(open(KERNEL_SOURCE, "rb").read()).hexdigest()
+        sha = kernel_sha256()
     except OSError:
         return None
     m = re.search(r"<!-- traffic-json (.*) -->", text)
@@ -1337,9 +1348,10 @@ def run_distill(args):
     torch.cuda.synchronize()
     floor_us = ev0.elapsed_time(ev1) * 1e3 / args.steps
     floor_bytes = 3 * n * vocab * 2
-    # algorithmic bytes of one evaluation: read both logit rows once, write the gradient once
-    alg = n * ((vocab + added) * 2 + vocab * 2 + (vocab + added) * 2)
-    alg_loss = n * ((vocab + added) * 2 + vocab * 2)
+    # algorithmic bytes of one evaluation: read every student row and the native rows' teacher
+    # rows once, write the gradient once
+    alg_loss = (n * (vocab + added) + int((kind == a2t.A2T_ROW_NATIVE).sum()) * vocab) * 2
+    alg = alg_loss + n * (vocab + added) * 2
     us = kern["distill_row"]["avg_us"]
     achieved = alg / (us * 1e-6) / 1e9
     base_line = None

@@ -54,6 +54,18 @@ def test_traffic_only_for_the_profiled_source(tmp_path, monkeypatch):
     assert bench.measured_traffic("stream", "attn_tile", [205, 225]) is None
 
 
+def test_traffic_hash_covers_the_headers(tmp_path, monkeypatch):
+    """An edit of a header that the profiled kernels compile in makes the figures stale too."""
+    import os
+    import re
+    included = re.findall(r'^#include "(\w+\.h)"', open(bench.KERNEL_SOURCE).read(), re.M)
+    assert {os.path.basename(p) for p in bench.KERNEL_HEADERS} >= set(included) - {"a2t.h"}
+    other = tmp_path / "device_common.h"
+    other.write_text(open(bench.KERNEL_HEADERS[0]).read() + "// edited\n")
+    monkeypatch.setattr(bench, "KERNEL_HEADERS", [str(other), *bench.KERNEL_HEADERS[1:]])
+    assert bench.measured_traffic("stream", "attn_tile", [205, 225]) is None
+
+
 def test_roofline_fields():
     kern = {"attn_tile": {"launches": 80, "avg_us": 10.0}}
     r = bench.roofline("attn_tile", kern, 17.2e6, "stream", [205, 225])
