@@ -394,7 +394,7 @@ constexpr int kBlockTilesPerCu = 6;
 // query rows per KV head in one pass over its keys and every further kBlockRows in
 // another.  Past two passes attn_block is the faster one, with its separate append
 // (36 layers' shape, 4 layers a step: 70 rows onto 500 keys 94 against 117 us, 1,024
-// onto 4,096 354 against 1,943).  With two passes it is where the launch has several
+// onto 4,096 357 against 1,943).  With two passes it is where the launch has several
 // tiles per CU to walk (160 query rows, 8 streams of ~2,400 keys: 185 against 234 us);
 // below that attn_tile's key splits fill the GPU and the append's launch costs more
 // (132 query rows, one stream of 4,096 keys: 88 against 82 us; 4 tiles per CU: 127

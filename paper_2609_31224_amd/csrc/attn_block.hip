@@ -14,11 +14,11 @@
 // products with the other's softmax.  32-row waves read each K and V operand from
 // LDS once for 32 query rows; the key halves give a SIMD its second wave where the
 // query blocks alone are one workgroup per CU (1,024 rows x 4 heads x 8 KV heads).
-// Measured there (head dim 128, 5,120 keys, 77 GFLOP a layer): 82 us, 0.94 PFLOP/s
-// (attn_tile with 27 key splits and their merge: 482 us); with no tile DMA after the
-// first step 69 us.  One wave of 64 rows per SIMD took 123 us, one of 32 rows x 64
-// keys 125 us, the halves held in opposite phases by barriers 83 us (and 18 instead
-// of 15.5 us on a 777-row prompt at head dim 64).
+// Measured there (head dim 128, 5,120 keys, 77 GFLOP a layer): 86 us, 0.90 PFLOP/s, the
+// matrix units busy 36 % of it (attn_tile with 27 key splits and their merge: 482 us).  Of
+// variants timed when it took 82 us: with no tile DMA after the first step 69 us; one wave
+// of 64 rows per SIMD 123, one of 32 rows x 64 keys 125, the halves held in opposite
+// phases by barriers 83 (and 18 instead of 15.5 us on a 777-row prompt at head dim 64).
 #include "a2t_internal.h"
 #include "device_common.h"
 

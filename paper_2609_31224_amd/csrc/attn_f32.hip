@@ -1,4 +1,5 @@
-// Causal attention of a step's rows for fp32 caches (gfx950): chunks and decode.
+// Causal attention of a step's rows for fp32 caches (gfx950): chunks and decode (but for decode
+// launches with one query head per KV head where attn_valu is the faster one).
 //
 //   attn_f32  one workgroup = (key split, QB blocks of 16 query rows, KV head,
 //             stream), 8 waves: wave w takes every eighth 16-key block of the split;
@@ -16,8 +17,8 @@
 // the next block's K and V are in flight while one is computed.
 //
 // Measured (2 streams of ~2,100 keys and 22 rows, 32/8 heads of 128, 1.7 GFLOP of products
-// with padding, 34 MB of K and V): a 4-layer step 896 -> 148 us, ~27 us of it each layer's
-// attention, where the vector ALU kernel (one workgroup per query row, 16 lanes per key)
+// with padding, 34 MB of K and V): a 4-layer step 896 -> 146 us, 27-28 us of it each layer's
+// attention with the matrix units busy 30 % of the time and 35 MB read, where the vector ALU kernel (one workgroup per query row, 16 lanes per key)
 // took 205 and the separate append 4.8; the products alone are 11 us and the bytes 6.  With 4
 // waves, with every load of a block waited for at once, or with two workgroups per CU it was
 // no faster.
