@@ -466,17 +466,20 @@ SplitCosts f32_costs(int head_dim, int query_blocks) {
 }
 
 // Whether an fp32 launch of one query row per KV head, already appended, runs on the vector
-// kernel, whose plan is given: a matrix product would fill one of its 16 query columns, and
-// what its workgroups do besides it takes longer.  Without splits it is the faster one (heads
-// of 128: 64 streams of 8 heads onto 100 keys 16.6 against 22.4 us, onto 1,500 136 against 150;
-// of 64: onto 500 28.2 against 32.9, onto 1,500 86.2 against 78.7); with splits at heads of 128
-// and long streams (16 streams of 8 heads, merge included: 500 keys 24 against 27.5 us, 300 25
-// against 19.7; at 64, 500 keys 22.1 against 18.4).
-bool f32_on_valu(int head_dim, int n, const int* tiles, const int* splits) {
+// kernel: a matrix product would fill one of its 16 query columns, and what its workgroups do
+// besides it takes longer.  The vector kernel is the faster one where it needs no key splits,
+// with one or two tiles a stream or streams that fill the CUs by themselves (64 streams of 8
+// heads of 128 onto 100 keys 16.6 against 22.4 us, onto 1,500 136 against 150; heads of 64 onto
+// 500 28.2 against 32.9, onto 1,500 86.2 against 78.7), and at heads of 128 with splits and
+// streams of 7 to 24 tiles (16 streams of 8 heads, merge included: 300 keys 25 against 19.7 us,
+// 500 24 against 27.5, 4 of 1,500 19.7 against 21.5; 64 uneven ones of 2 heads and up to 2,480
+// keys, 2 layers, 122 against 111; at 64, 500 keys 22.1 against 18.4).
+bool f32_on_valu(const a2t_cache* c, int n, const int* tiles) {
     const int longest = *std::max_element(tiles, tiles + n);
-    const bool whole = *std::max_element(splits, splits + n) == 1;
-    return head_dim == 128 ? whole || longest > 6 : whole && longest <= 16;
+    const bool whole = longest <= 2 || (int64_t)n * c->cfg.n_kv_heads >= c->target_wgs;
+    return c->cfg.head_dim == 128 ? whole || (longest > 6 && longest <= 24) : whole && longest <= 16;
 }
+constexpr SplitCosts kValuCosts{4, 2, 1 << 20, 2};
 
 // Where a launch's split partials go: the cache's workspace (default) or the
 // library's fixed device array (the no-allocation entry point, which plans
@@ -537,22 +540,17 @@ int attn_launch(a2t_cache* c, int layer, int n, const int32_t* ids, const int32_
         floats[i] = (int64_t)c->cfg.n_kv_heads * G * n_q[i] * rf;
     }
     const bool block = !in_row0 && many_rows(c, n, ids, n_q);
-    if (f32 && !in_row0 && !wsc && G == 1 && max_rows == 1) {
-        plan_splits(c, n, tiles, floats, nsplit, c->dev.ws_floats);
-        valu = f32_on_valu(c->cfg.head_dim, n, tiles, nsplit);
-        f32 = !valu;
-    }
-    if (valu && !c->force_valu) {
-        // planned above
-    } else if (f32 || block) {
+    const bool one_row = f32 && !in_row0 && !wsc && G == 1 && max_rows == 1 && f32_on_valu(c, n, tiles);
+    if (one_row) f32 = false, valu = true;
+    if (f32 || block || one_row) {
         SplitStream ss[kMaxDesc];
         if (f32) query_blocks = f32_query_blocks(c, n, tiles, n_q);
         for (int i = 0; i < n; ++i) {
             const int rows = G * n_q[i];
             ss[i] = {tiles[i], c->cfg.n_kv_heads * (f32 ? f32_groups(rows, query_blocks) : (rows + kBlockRows - 1) / kBlockRows),
-                     floats[i]};
+                     floats[i]};   // one row: one workgroup
         }
-        c->planner.plan(n, ss, f32 ? f32_costs(c->cfg.head_dim, query_blocks) : kBlockCosts, c->target_wgs, c->force_splits,
+        c->planner.plan(n, ss, f32 ? f32_costs(c->cfg.head_dim, query_blocks) : block ? kBlockCosts : kValuCosts, c->target_wgs, c->force_splits,
                         wsc ? wsc->floats : c->dev.ws_floats, nsplit);
     } else {
         plan_splits(c, n, tiles, floats, nsplit, wsc ? INT64_MAX : c->dev.ws_floats);

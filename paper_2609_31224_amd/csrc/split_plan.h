@@ -76,8 +76,12 @@ public:
         } else {
             try_.resize(n);
             int64_t best = INT64_MAX, best_wgs = 0;
-            // budgets a sixteenth apart; the last one splits nothing
+            // budgets a sixteenth apart; the last one splits nothing.  The longest stream's
+            // workgroups only get longer with the budget: once they alone take more than the
+            // best launch so far, no later budget is better.
             for (int budget = std::min(costs.min_tiles, max_tiles);; budget = std::min(max_tiles, budget + std::max(1, budget / 16))) {
+                const int cut = std::min((max_tiles + budget - 1) / budget, kMaxSplits);
+                if ((max_tiles + cut - 1) / cut + costs.fixed > best) break;
                 int64_t wgs = 0, ws = 0;
                 bool any = false;
                 for (int i = 0; i < n; ++i) {

@@ -160,19 +160,21 @@ def test_masked_values_stay_out_of_two_blocks(gpu, monkeypatch, d, rows, bad, sp
     assert np.isnan(outs[1][bad:]).all()
 
 
-@pytest.mark.parametrize("hkv,d,prefix,splits,valu", [
-    (1, 64, 0, None, True), (1, 64, 60, None, True),      # one and two tiles: no splits
-    (3, 128, 0, None, True), (3, 128, 200, None, False),  # four tiles, split
-    (3, 128, 500, None, True),                            # eight tiles of 128 dims, split
-    (2, 64, 300, "1", True), (2, 64, 300, "3", False),
-    (2, 64, 1024, "1", False),                            # 17 tiles of 64 dims
+@pytest.mark.parametrize("hkv,d,prefix,splits,target,valu", [
+    (1, 64, 0, None, None, True), (1, 64, 60, None, None, True),      # one and two tiles
+    (3, 128, 0, None, None, True), (3, 128, 200, None, None, False),  # four tiles
+    (3, 128, 500, None, None, True), (3, 128, 500, "3", None, True),  # eight tiles of 128 dims
+    (2, 64, 300, None, None, False),
+    (2, 64, 300, None, "2", True), (2, 64, 300, "3", "2", True),      # two heads fill two CUs
+    (2, 64, 1024, None, "2", False),                                  # 17 tiles of 64 dims
 ])
-def test_f32_one_query_row(gpu, monkeypatch, hkv, d, prefix, splits, valu):
+def test_f32_one_query_row(gpu, monkeypatch, hkv, d, prefix, splits, target, valu):
     """Decode rows with one query head per KV head: on the vector kernel where it is the faster
     one, on attn_f32 elsewhere, the oracle's results on both."""
     import paper_2609_31224_amd as a2t
-    if splits:
-        monkeypatch.setenv("A2T_SPLITS", splits)
+    for name, value in (("A2T_SPLITS", splits), ("A2T_TARGET_WGS", target)):
+        if value:
+            monkeypatch.setenv(name, value)
     cfg = dataclasses.replace(CONFIGS[0], n_q_heads=hkv, n_kv_heads=hkv, head_dim=d)
     spec = tiny_stream([SMALL, [SEG_RESPONSE], [SEG_RESPONSE], SMALL, [SEG_RESPONSE], SMALL, [SEG_RESPONSE]], prefix=prefix)
     bounds = row_bounds(spec)
