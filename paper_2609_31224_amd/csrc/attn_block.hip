@@ -88,8 +88,9 @@ __device__ __forceinline__ int v_swizzle(int row) {
     return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1);
 }
 
-template <int D, class BT>
-__global__ __launch_bounds__(kBlockThreads) void attn_block_kernel(DevState st, BT b, const uint16_t* q, uint16_t* o) {
+template <int D, int N>
+__global__ __launch_bounds__(kBlockThreads) void attn_block_kernel(DevState st, AttnBatchT<N> b, WgStart<N> start,
+                                                                   const uint16_t* q, uint16_t* o) {
     constexpr int KS = D / 16;                 // k-steps of Q.K^T
     constexpr int DB = D / 32;                 // 32-dim blocks of O
     constexpr int CPR = D / 8;                 // 16-byte chunks per row
@@ -100,14 +101,15 @@ __global__ __launch_bounds__(kBlockThreads) void attn_block_kernel(DevState st, 
     __shared__ float2 s_ml[4][64];
     static_assert(8 * TILE * 2 >= 4 * DB * 16 * 256, "the second key half's sums fit the ring");
 
-    const AttnDesc d = b.d[blockIdx.z];
+    int wg;
+    const AttnDesc d = b.d[stream_of(start, b.count, &wg)];
     const int G = st.G, nq = d.n_q, M = G * nq, R = d.R;
     const int nqb = (M + kBlockRows - 1) / kBlockRows;
     auto uniform = [](int x) { return __builtin_amdgcn_readfirstlane(x); };   // divisions run on the vector ALU
     // linear block (split, query block, KV head), heads fastest: the workgroups of
     // a head share an XCD's L2 when the head count divides the 8 XCDs, and the
     // later query blocks, which see the most keys, are dispatched first
-    const int y = uniform(blockIdx.x / st.Hkv), g = blockIdx.x - y * st.Hkv;
+    const int y = uniform(wg / st.Hkv), g = wg - y * st.Hkv;
     const int sp = uniform(y / nqb), qb = nqb - 1 - (y - sp * nqb);
     if (sp >= d.splits) return;
     const int w = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63, l32 = lane & 31, h = lane >> 5;
@@ -428,25 +430,23 @@ __global__ __launch_bounds__(kBlockThreads) void attn_block_kernel(DevState st, 
 
 hipError_t launch_attn_block(const DevState& st, const AttnBatch& b, const void* q, void* o, hipStream_t stream,
                              const KTimer& kt) {
-    int wgs = 0;
-    for (int i = 0; i < b.count; ++i) {
-        const int n = (st.G * b.d[i].n_q + kBlockRows - 1) / kBlockRows * b.d[i].splits * st.Hkv;
-        wgs = n > wgs ? n : wgs;
-    }
-    const dim3 grid(wgs, 1, b.count);
     const uint16_t* qq = static_cast<const uint16_t*>(q);
     uint16_t* oo = static_cast<uint16_t*>(o);
     return by_size<AttnBatchT>(b, [&](const auto& bb) {
-        using B = std::decay_t<decltype(bb)>;
+        constexpr int N = sizeof(bb.d) / sizeof(bb.d[0]);
+        WgStart<N> start{};
+        const dim3 grid = place_workgroups(b.count, &start, [&](int i) {
+            return (st.G * b.d[i].n_q + kBlockRows - 1) / kBlockRows * b.d[i].splits * st.Hkv;
+        });
         auto go = [&](auto kernel) {
             if (kt.start)
-                hipExtLaunchKernelGGL(kernel, grid, dim3(kBlockThreads), 0, stream, kt.start, kt.stop, 0, st, bb, qq, oo);
+                hipExtLaunchKernelGGL(kernel, grid, dim3(kBlockThreads), 0, stream, kt.start, kt.stop, 0, st, bb, start, qq, oo);
             else
-                hipLaunchKernelGGL(kernel, grid, dim3(kBlockThreads), 0, stream, st, bb, qq, oo);
+                hipLaunchKernelGGL(kernel, grid, dim3(kBlockThreads), 0, stream, st, bb, start, qq, oo);
             return hipGetLastError();
         };
-        if (st.D == 128) return go(attn_block_kernel<128, B>);
-        if (st.D == 64) return go(attn_block_kernel<64, B>);
+        if (st.D == 128) return go(attn_block_kernel<128, N>);
+        if (st.D == 64) return go(attn_block_kernel<64, N>);
         return hipErrorInvalidValue;
     });
 }

@@ -78,9 +78,10 @@ __device__ __forceinline__ float col_sum(float x) {
 //            in the lane), A = V of key 4 lg + r; row i of product (b, j) is dim
 //            64 b + 4 i + j, so a lane needs V at 64 b + 4 (l % 16) .. + 3; it gets
 //            dims 64 b + 16 lg + 4 e + j.
-template <int D, int QB, class BT>
-__global__ __launch_bounds__(64 * kKeyWaves, 2) void attn_f32_kernel(DevState st, BT b, const float* q, float* o,
-                                                                          const float* k_in, const float* v_in) {
+template <int D, int QB, int N>
+__global__ __launch_bounds__(64 * kKeyWaves, 2) void attn_f32_kernel(DevState st, AttnBatchT<N> b, WgStart<N> start,
+                                                                     const float* q, float* o, const float* k_in,
+                                                                     const float* v_in) {
     constexpr int KS = D / 16;   // 16-byte K loads of a lane per key block
     constexpr int NB = D / 64;   // 16-byte V loads of a lane per key
     constexpr int kScoreSums = 4;
@@ -95,13 +96,14 @@ __global__ __launch_bounds__(64 * kKeyWaves, 2) void attn_f32_kernel(DevState st
     f32x4* const s_k = s_mem + QB * KS * 64 + (threadIdx.x >> 6) * (kKeyBlock * CPR);
     static_assert(QB * KS * 64 + kKeyWaves * kKeyBlock * CPR <= QB * kKeyWaves * 4 * NB * 64 + kExtra, "they fit");
 
-    const AttnDesc d = b.d[blockIdx.z];
+    int wg;
+    const AttnDesc d = b.d[stream_of(start, b.count, &wg)];
     const int G = st.G, M = G * d.n_q, R = d.R;
     const int blocks = (M + kKeyBlock - 1) / kKeyBlock, groups = (blocks + QB - 1) / QB;
     auto uniform = [](int x) { return __builtin_amdgcn_readfirstlane(x); };   // divisions run on the vector ALU
     // linear block (split, query group, KV head), heads fastest: the workgroups of a head
     // share an XCD's L2 when the head count divides the 8 XCDs
-    const int y = uniform(blockIdx.x / st.Hkv), g = blockIdx.x - y * st.Hkv;
+    const int y = uniform(wg / st.Hkv), g = wg - y * st.Hkv;
     const int sp = uniform(y / groups), grp = groups - 1 - (y - sp * groups);
     if (sp >= d.splits) return;
     const int w = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63, l16 = lane & 15, lg = lane >> 4;
@@ -444,25 +446,24 @@ __global__ __launch_bounds__(64 * kKeyWaves, 2) void attn_f32_kernel(DevState st
 
 hipError_t launch_attn_f32(const DevState& st, const AttnBatch& b, int query_blocks, const void* q, void* o,
                            const void* k_in, const void* v_in, hipStream_t stream, const KTimer& kt) {
-    int wgs = 0;
-    for (int i = 0; i < b.count; ++i) {
-        const int n = f32_groups(st.G * b.d[i].n_q, query_blocks) * b.d[i].splits * st.Hkv;
-        wgs = n > wgs ? n : wgs;
-    }
-    const dim3 grid(wgs, 1, b.count), block(64 * kKeyWaves);
+    const dim3 block(64 * kKeyWaves);
     const float *qq = static_cast<const float*>(q), *ki = static_cast<const float*>(k_in), *vi = static_cast<const float*>(v_in);
     float* oo = static_cast<float*>(o);
     return by_size<AttnBatchT>(b, [&](const auto& bb) {
-        using B = std::decay_t<decltype(bb)>;
+        constexpr int N = sizeof(bb.d) / sizeof(bb.d[0]);
+        WgStart<N> start{};
+        const dim3 grid = place_workgroups(b.count, &start, [&](int i) {
+            return f32_groups(st.G * b.d[i].n_q, query_blocks) * b.d[i].splits * st.Hkv;
+        });
         auto go = [&](auto kernel) {
             if (kt.start)
-                hipExtLaunchKernelGGL(kernel, grid, block, 0, stream, kt.start, kt.stop, 0, st, bb, qq, oo, ki, vi);
+                hipExtLaunchKernelGGL(kernel, grid, block, 0, stream, kt.start, kt.stop, 0, st, bb, start, qq, oo, ki, vi);
             else
-                hipLaunchKernelGGL(kernel, grid, block, 0, stream, st, bb, qq, oo, ki, vi);
+                hipLaunchKernelGGL(kernel, grid, block, 0, stream, st, bb, start, qq, oo, ki, vi);
             return hipGetLastError();
         };
-        if (st.D == 128) return query_blocks == 1 ? go(attn_f32_kernel<128, 1, B>) : go(attn_f32_kernel<128, 2, B>);
-        if (st.D == 64) return query_blocks == 1 ? go(attn_f32_kernel<64, 1, B>) : go(attn_f32_kernel<64, 2, B>);
+        if (st.D == 128) return query_blocks == 1 ? go(attn_f32_kernel<128, 1, N>) : go(attn_f32_kernel<128, 2, N>);
+        if (st.D == 64) return query_blocks == 1 ? go(attn_f32_kernel<64, 1, N>) : go(attn_f32_kernel<64, 2, N>);
         return hipErrorInvalidValue;
     });
 }

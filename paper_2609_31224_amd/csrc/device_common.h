@@ -1,6 +1,8 @@
 // Device helpers shared by the attention kernels (gfx950).
 #pragma once
 
+#include "a2t_internal.h"
+
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -27,6 +29,35 @@ template <int N>
 __device__ __forceinline__ void wait_vmem() {
     static_assert(N >= 0 && N < 64, "vmcnt range");
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+// Stream of a workgroup, and the workgroup's place among the stream's.  Launches of uneven
+// streams have no empty workgroups (place_workgroups): the dispatcher hands workgroups to the
+// shader engines in turn, empty ones too, so that the real ones of small streams all went to
+// one or two of an XCD's four engines where the largest stream had four or two query blocks (30
+// streams of one row onto 2,500 keys beside one of 40, 90 or 400 rows, 8 KV heads of 128: 95,
+// 69 and 168 us; without gaps 61, 68 and 73).
+template <int N>
+__device__ __forceinline__ int stream_of(const WgStart<N>& start, int count, int* place) {
+    if (N == 1 || start.first[0] < 0) {
+        *place = blockIdx.x;
+        return blockIdx.z;
+    }
+    if (N <= 8) {   // scalar loads and compares
+        int z = 0, at = 0;
+#pragma unroll
+        for (int i = 1; i < N; ++i) {
+            const bool past = i < count && (int)blockIdx.x >= start.first[i];
+            z = past ? i : z;
+            at = past ? start.first[i] : at;
+        }
+        *place = (int)blockIdx.x - at;
+        return z;
+    }
+    const int lane = threadIdx.x & 63;
+    const int first = lane < count ? start.first[lane < N ? lane : 0] : 0x7fffffff;
+    const int z = __builtin_popcountll(__ballot((int)blockIdx.x >= first)) - 1;
+    *place = (int)blockIdx.x - __builtin_amdgcn_readlane(first, z);
+    return z;
 }
 // workgroup barrier that the compiler may not move memory accesses across; no
 // memory fence (the waits that make DMA'd data visible are explicit)
