@@ -154,6 +154,9 @@ struct a2t_cache {
     std::vector<int> plan_tiles, plan_splits, plan_tmp, plan_order;
     std::vector<int64_t> plan_heap;
     SplitPlanner planner;            // of attn_block and attn_f32 launches
+    SplitPlanner route_tile, route_block;   // the kernels that a mixed launch is weighed for
+    std::vector<SplitStream> route_key;     // the last launch that was, and the choice
+    bool route_many = false;
     bool force_valu = false;
     // profiling
     bool prof_on = false;
@@ -388,54 +391,77 @@ void plan_splits(a2t_cache* c, int n, const int* tiles, const int64_t* floats_pe
     c->plan_splits.assign(splits, splits + n);
 }
 
-constexpr int kBlockTilesPerCu = 6;
-
-// Whether a launch runs on attn_block instead of attn_tile, which takes kBlockRows
-// query rows per KV head in one pass over its keys and every further kBlockRows in
-// another.  Past two passes attn_block is the faster one, with its separate append
-// (36 layers' shape, 4 layers a step: 70 rows onto 500 keys 94 against 117 us, 1,024
-// onto 4,096 357 against 1,943).  With two passes it is where the launch has several
-// tiles per CU to walk (160 query rows, 8 streams of ~2,400 keys: 185 against 234 us);
-// below that attn_tile's key splits fill the GPU and the append's launch costs more
-// (132 query rows, one stream of 4,096 keys: 88 against 82 us; 4 tiles per CU: 127
-// against 124).
-//
-// Beside streams of one pass, which attn_tile reads at a fifth more bytes a second, the
-// streams of many passes may keep a launch there: a workgroup of attn_tile walks its passes
-// one after the other (a tile takes ~1.4 us, a pass besides it ~6, a tile of new rows, which
-// every pass rotates again, ~5), and as long as it ends with the others nothing is gained.
-// `extra` rows are added to each stream's resident count (a step that is about to be
-// appended).  Four layers of 32/8 heads of 128, attn_tile against attn_block: 100 rows onto
-// 100 keys beside 15 streams of 22 rows onto 8,192 keys 412 against 631 us, 65 rows beside 63
-// streams of one row onto ~2,900 keys 597 against 664; 70 rows beside 20 streams of 22 rows
-// onto ~2,300 keys 387 against 242.
-bool many_rows(const a2t_cache* c, int n, const int32_t* ids, const int32_t* n_q, const int32_t* extra = nullptr) {
-    if (c->cfg.dtype != A2T_BF16 || c->force_valu) return false;
-    const int64_t G = c->cfg.n_q_heads / c->cfg.n_kv_heads, Hkv = c->cfg.n_kv_heads;
-    // in tiles; row counts are not checked yet where an append follows
-    int64_t rows = 0, tiles = 0, single = 0, chain = 0;
-    for (int i = 0; i < n; ++i) {
-        const int64_t t = ((int64_t)c->ss[ids[i]].resident() + (extra ? extra[i] : 0) + kTileKeys - 1) / kTileKeys;
-        const int64_t passes = (G * n_q[i] + kBlockRows - 1) / kBlockRows;
-        rows = std::max<int64_t>(rows, n_q[i]);
-        tiles += t;
-        if (passes == 1) {
-            single += t;
-        } else {
-            const int64_t fresh = std::min(t, ((int64_t)n_q[i] + kTileKeys - 1) / kTileKeys);
-            chain = std::max(chain, passes * (4 + (t - fresh) + 7 * fresh / 2));
-        }
-    }
-    if (single && 4 * chain <= 5 * single * Hkv / c->target_wgs + 28) return false;
-    return G * rows > 2 * kBlockRows || (G * rows > kBlockRows && tiles * Hkv >= (int64_t)kBlockTilesPerCu * c->target_wgs);
-}
-
 // What attn_block's workgroups cost: a tile 0.7 to 1 us, the rest of one ~14, a merge launch
 // ~5 and as much again for 5 M floats of partials.  Measured at 1 to 16 splits (32/8 heads of
 // 128; us with 1, 2, 4 splits, merge included): five streams of 90 rows onto 2,000 keys 39.8,
 // 33.2, 41.2; eight of 65 rows 41.7, 63.0, 72.3; five of 256 rows onto 2,048 keys 83.7, 87.6,
 // 96.4; one of 65 rows and 15 of 22 rows onto 8,192 keys 150.0, 157.7, 141.6 (3 splits 126.6).
 constexpr SplitCosts kBlockCosts{16, 6, 1 << 20, 4};
+
+constexpr int kBlockTilesPerCu = 6;
+
+// Whether a launch runs on attn_block instead of attn_tile, which takes kBlockRows
+// query rows per KV head in one pass over its keys and every further kBlockRows in
+// another.
+//
+// Streams of several passes alone: past two passes attn_block is the faster one, with its
+// separate append (36 layers' shape, 4 layers a step: 70 rows onto 500 keys 94 against 117 us,
+// 1,024 onto 4,096 357 against 1,943).  With two passes it is where the launch has several
+// tiles per CU to walk (160 query rows, 8 streams of ~2,400 keys: 185 against 234 us);
+// below that attn_tile's key splits fill the GPU and the append's launch costs more
+// (132 query rows, one stream of 4,096 keys: 88 against 82 us; 4 tiles per CU: 127
+// against 124).
+//
+// Beside streams of one pass both launches are estimated from their plans.  attn_tile: a
+// tile takes 1.4 us at head dim 128 and a workgroup 4 tiles besides, its passes run one after
+// the other and each of them rotates the step's own keys again (a tile of them 3.5), and all
+// keys arrive at 5.9 TB/s; attn_block: 0.85 us a tile and 5.5 TB/s after the first 12 us; merges 5 to
+// 7 us, the separate append 4.7.  Over 69 mixed launches (a long step of 40 to 700 rows beside 3
+// to 60 streams of 1 or 22 rows) the choice costs 0.2 % against the better kernel of each on
+// average, at most 11 %.  Us of both kernels, appends and merges included, 32/8 heads of 128: 40
+// rows beside 60 streams of one row onto 3,500 keys 148 / 167, 100 rows beside 15 units onto
+// 8,192 keys 105 / 115, 40 rows beside 20 units onto ~2,300 74 / 56, 90 rows beside 8 units
+// onto 8,192 90 / 73, a 300-row prompt beside 60 single rows 306 / 171.
+//
+// `extra` rows are added to each stream's resident count (a step that is about to be
+// appended).
+bool many_rows(a2t_cache* c, int n, const int32_t* ids, const int32_t* n_q, const int32_t* extra = nullptr) {
+    if (c->cfg.dtype != A2T_BF16 || c->force_valu) return false;
+    const int G = c->cfg.n_q_heads / c->cfg.n_kv_heads, Hkv = c->cfg.n_kv_heads, D = c->cfg.head_dim;
+    SplitStream tile[kMaxDesc], block[kMaxDesc];
+    int splits[kMaxDesc];
+    int rows = 0, single = 0;
+    int64_t tiles = 0;
+    for (int i = 0; i < n; ++i) {
+        // row counts are not checked yet where an append follows, and refuses these
+        if (n_q[i] > c->cfg.max_step_rows) return false;
+        const int64_t R = (int64_t)c->ss[ids[i]].resident() + (extra ? std::min(extra[i], c->cfg.max_step_rows) : 0);
+        const int t = (int)std::max<int64_t>(1, (R + kTileKeys - 1) / kTileKeys), blocks = (G * n_q[i] + kBlockRows - 1) / kBlockRows;
+        const int64_t floats = (int64_t)Hkv * G * n_q[i] * partial_row_floats(D, false);
+        tile[i] = {t, Hkv, floats};
+        block[i] = {t, Hkv * blocks, floats};
+        rows = std::max(rows, n_q[i]);
+        single += blocks == 1;
+        tiles += t;
+    }
+    if (G * rows <= kBlockRows) return false;
+    if (!single) return G * rows > 2 * kBlockRows || tiles * Hkv >= (int64_t)kBlockTilesPerCu * c->target_wgs;
+    if ((int)c->route_key.size() == n && std::equal(block, block + n, c->route_key.begin())) return c->route_many;
+    const double scale = D == 128 ? 1.0 : 0.6, mb = (double)tiles * Hkv * kTileKeys * D * 4 / 1e6;   // of K and V
+    c->route_tile.plan(n, tile, SplitCosts{4, 0, INT64_MAX, 2}, c->target_wgs, 0, INT64_MAX, splits);
+    const int64_t half = c->route_tile.dispatch(n, tile, splits, c->target_wgs, [&](int i) {   // in half tiles
+        const int64_t per = (tile[i].tiles + splits[i] - 1) / splits[i], fresh = std::min<int64_t>(per, (n_q[i] + kTileKeys - 1) / kTileKeys);
+        const int64_t passes = (G * n_q[i] + kBlockRows - 1) / kBlockRows;
+        return passes == 1 ? 2 * (4 + per) : passes * (2 * (4 + per - fresh) + 7 * fresh);
+    });
+    const bool split_tile = *std::max_element(splits, splits + n) > 1;
+    const double us_tile = std::max(0.7 * scale * (double)half, mb / 5.9 + 6) + (split_tile ? 7 : 0);
+    c->route_block.plan(n, block, kBlockCosts, c->target_wgs, 0, c->dev.ws_floats, splits);
+    const bool split_block = *std::max_element(splits, splits + n) > 1;
+    const double us_block = std::max(0.85 * scale * (double)c->route_block.cost(), mb / 5.5 + 12) + 4.7 + (split_block ? 5 : 0);
+    c->route_key.assign(block, block + n);
+    return c->route_many = us_tile > 0.95 * us_block;
+}
 
 // An attn_f32 launch: query blocks per workgroup, and what its workgroups cost.
 //
@@ -781,7 +807,8 @@ int a2t_cache_create(const a2t_config* cfg, void* hip_stream, a2t_cache** out) {
     // the split planner's scratch, so that no attention call allocates
     for (auto* v : {&c->plan_tiles, &c->plan_splits, &c->plan_tmp, &c->plan_order}) v->reserve(kMaxDesc);
     c->plan_heap.reserve((size_t)c->target_wgs);
-    c->planner.reserve(kMaxDesc, c->target_wgs);
+    for (SplitPlanner* p : {&c->planner, &c->route_tile, &c->route_block}) p->reserve(kMaxDesc, c->target_wgs);
+    c->route_key.reserve(kMaxDesc);
 
     DevState& d = c->dev;
     d.L = k.n_layers;

@@ -64,6 +64,7 @@ public:
             return;
         }
         splits_.assign(n, 1);
+        cost_ = 0;
         int max_tiles = 1;
         for (int i = 0; i < n; ++i) max_tiles = std::max(max_tiles, s[i].tiles);
         if (force > 0) {
@@ -93,7 +94,7 @@ public:
                 if (ws <= ws_limit) {
                     const int64_t t = makespan(n, s, try_.data(), costs.fixed, slots) + (any ? costs.merge + ws / costs.merge_floats : 0);
                     if (t < best || (t == best && wgs < best_wgs)) {
-                        best = t;
+                        best = cost_ = t;
                         best_wgs = wgs;
                         splits_.assign(try_.begin(), try_.end());
                     }
@@ -106,9 +107,19 @@ public:
         std::copy(splits_.begin(), splits_.end(), splits);
     }
 
-    // when the last workgroup ends, the streams with the longest workgroups dispatched first
+    // what the last plan takes, in tiles, its merge included (0 where the splits were forced)
+    int64_t cost() const { return cost_; }
+
+    // when the last workgroup ends
     int64_t makespan(int n, const SplitStream* s, const int* splits, int fixed, int slots) {
-        auto cost = [&](int i) { return (int64_t)(s[i].tiles + splits[i] - 1) / splits[i] + fixed; };
+        return dispatch(n, s, splits, slots, [&](int i) { return (int64_t)(s[i].tiles + splits[i] - 1) / splits[i] + fixed; });
+    }
+
+    // the same with a cost of its own for each stream's workgroups; the streams with the most
+    // tiles a workgroup are dispatched first
+    template <class Cost>
+    int64_t dispatch(int n, const SplitStream* s, const int* splits, int slots, Cost&& cost) {
+        auto per = [&](int i) { return (s[i].tiles + splits[i] - 1) / splits[i]; };
         int64_t wgs = 0, longest = 0;
         order_.resize(n);
         for (int i = 0; i < n; ++i) {
@@ -117,7 +128,7 @@ public:
             longest = std::max(longest, cost(i));
         }
         if (wgs <= slots) return longest;
-        std::sort(order_.begin(), order_.end(), [&](int a, int b) { return cost(a) != cost(b) ? cost(a) > cost(b) : a < b; });
+        std::sort(order_.begin(), order_.end(), [&](int a, int b) { return per(a) != per(b) ? per(a) > per(b) : a < b; });
         // (time, CUs that are free from then on), by falling time
         levels_.clear();
         levels_.push_back({0, slots});
@@ -143,7 +154,7 @@ private:
     std::vector<std::pair<int64_t, int64_t>> levels_;
     SplitCosts costs_{};
     int force_ = -1, slots_ = -1;
-    int64_t limit_ = -1;
+    int64_t limit_ = -1, cost_ = 0;
 };
 
 }  // namespace a2t
