@@ -2,9 +2,10 @@
 the fp64 oracle at every step: row counts around the 128-row blocks and the 256-row
 threshold of the dispatch, one to eight query heads per KV head, both head dims, key
 counts around the 64-key tiles, a ring that wraps, a kept region, forced and planned
-key splits, fewer queries than rows, and batches whose streams differ.
+key splits, fewer queries than rows, and batches of 2 to 64 streams that differ.
 
-Bar: 2e-2 for bf16 caches with fp32 accumulation, as everywhere in this suite.
+Bars: 2e-2 for bf16 caches with fp32 accumulation, 1e-4 for fp32 ones, as everywhere in this
+suite.
 """
 import dataclasses
 import os
@@ -17,6 +18,7 @@ from tests.harness import Lockstep, row_bounds
 pytestmark = pytest.mark.gpu
 
 BF16_TOL = 2e-2
+F32_TOL = 1e-4
 
 
 def _long(n):
@@ -141,8 +143,9 @@ def test_infinite_values(gpu, d, splits, monkeypatch):
 def test_mixed_batch_routes(gpu, monkeypatch, target, tile, block, fused):
     """A batch of one stream with several passes of query rows among streams of one pass: it
     stays on attn_tile where the others' work outlasts its passes (here: all on one CU, which
-    attn_block's workgroups occupy for longer) and runs on attn_block where it does not, with the oracle's results on either.  Of the three steps the
-    first holds the other streams' prefixes, many rows each, and the last no long unit."""
+    attn_block's workgroups occupy for longer) and runs on attn_block where it does not, with the
+    oracle's results on either.  Of the three steps the first holds the other streams' prefixes,
+    many rows each, and the last no long unit."""
     import paper_2609_31224_amd as a2t
     if target:
         monkeypatch.setenv("A2T_TARGET_WGS", target)
@@ -156,5 +159,32 @@ def test_mixed_batch_routes(gpu, monkeypatch, target, tile, block, fused):
     try:
         ls.run()
         assert [a2t.a2t_kernel_time(ls.cache, n)[0] for n in ("attn_tile", "attn_block")] == [tile, block]
+    finally:
+        ls.close()
+
+
+@pytest.mark.parametrize("n", [2, 8, 9, 21, 64])
+@pytest.mark.parametrize("dtype,kernel,tol", [("bf16", "attn_block", BF16_TOL), ("f32", "attn_f32", F32_TOL)])
+def test_uneven_streams(gpu, monkeypatch, dtype, kernel, tol, n):
+    """One long step among streams of one to five rows onto one or two tiles of keys, in the
+    first, an inner and the last place, two splits a stream where its tiles allow: the streams'
+    workgroups follow each other, and each finds its stream by compares with up to 8 streams,
+    by a ballot beyond."""
+    import paper_2609_31224_amd as a2t
+    monkeypatch.setenv("A2T_SPLITS", "2")
+    cfg = dataclasses.replace(CONFIGS[0], n_q_heads=4, n_kv_heads=1, head_dim=64)
+    longs = [0, n // 2, n - 1]
+    specs = []
+    for s in range(n):
+        units = [_long(70) if s == at else [SEG_ACOUSTIC] * (1 + (s + at) % 5) for at in longs]
+        specs.append(dataclasses.replace(tiny_stream(units, prefix=20 + 70 * (s % 3 == 1)), stream=s))
+    bounds = [row_bounds(s) for s in specs]
+    ls = Lockstep(cfg, 9, specs, layers_checked=[0], n_layers=1, budgets=[400] * n, window=1,
+                  unit_rows=max(b[0] for b in bounds), kept_rows=max(b[1] for b in bounds) + 1,
+                  max_step=max(b[2] for b in bounds), tol=tol, dtype=dtype, fused=True)
+    a2t.a2t_profile_enable(ls.cache, kernel)
+    try:
+        ls.run()
+        assert a2t.a2t_kernel_time(ls.cache, kernel)[0] >= len(longs)
     finally:
         ls.close()
